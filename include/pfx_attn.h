@@ -169,10 +169,11 @@ typedef struct pfx_plan_opts {
    * are pieces).  The work division does not depend on it, only its
    * timing. */
   int32_t decode_workers;
-  /* Longest decode piece, in 32-key steps (0 = automatic: 16, or 64 when
-   * the decode items hold at least 32768 steps; at most 64).  Shorter pieces
-   * balance the workgroups better but give each decode row more partial
-   * results to merge. */
+  /* Longest decode piece, in 32-key steps (0 = automatic: 64 when the decode
+   * items hold at least 32768 steps, 32 from 12288, otherwise at most 16 and
+   * as short as keeps all workgroups resident at once, 3 at least; at most
+   * 64).  Shorter pieces balance the workgroups better but give each decode
+   * row more partial results to merge. */
   int32_t piece_steps;
   /* Engine of the decode pieces: PFX_DECODE_MFMA (0, the default: matrix
    * cores, and wide prefix blocks for agents with more than 64 decode

@@ -1473,95 +1473,204 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(AttnArgs a) {
 // any is used.
 constexpr int kMergeBatch = 8;
 
-// F: the append of this step is folded in.  The decode launch read every
-// decode token's new K/V straight from k_new / v_new; the merge, which runs
-// after it, writes them into their pool slots (2 Hkv D / 8 chunks of 16
-// bytes per token, spread over the token's threads).
-template <int D, bool F>
-__global__ __launch_bounds__(128) void merge_rows_kernel(AttnArgs a, int n_tok) {
+// What one merge thread works on: token row m, query head qh, 16-byte unit
+// (grp, blk pair) of the row.
+struct MergeSpot {
+  int m, qh, sl, grp, blk;
+};
+
+template <int D>
+__device__ __forceinline__ MergeSpot merge_spot(const AttnArgs& a, size_t t) {
   constexpr int CH = D / 16;
   constexpr int SL = D / 8;  // threads per row: 4 groups x CH/2 pairs
-  const size_t t = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= size_t(n_tok) * a.hq * SL) return;
-  const int sl = int(t % SL);
-  const int grp = sl / (CH / 2), blk = 2 * (sl % (CH / 2));
-  const int qh = int((t / SL) % a.hq);
-  const int m = int(t / (size_t(SL) * a.hq));
-  // The append's chunks (at most two per thread: 2 Hkv <= 2 Hq), loaded
-  // beside the merge's own loads and stored at the end.
-  constexpr int kAppendPerThread = 2;
-  u32x4 app_val[kAppendPerThread];
-  uint16_t* app_dst[kAppendPerThread] = {nullptr, nullptr};
-  if constexpr (F) {
-    const int tok = a.merge_tok_is_row ? m : a.plan.merge_tok[m];
-    const int slot = a.plan.tok_slot[tok];
-    const int per = a.hkv * SL;  // chunks of K (or V) per token
+  MergeSpot s;
+  s.sl = int(t % SL);
+  s.grp = s.sl / (CH / 2);
+  s.blk = 2 * (s.sl % (CH / 2));
+  s.qh = int((t / SL) % a.hq);
+  s.m = int(t / (size_t(SL) * a.hq));
+  return s;
+}
+
+// The append's share of one merge thread, loaded beside the merge's own loads
+// and stored at the end: at most two 16-byte chunks (2 Hkv <= 2 Hq).
+struct MergeAppend {
+  static constexpr int kMost = 2;
+  u32x4 val[kMost];
+  uint16_t* dst[kMost] = {nullptr, nullptr};
+};
+
+template <int D>
+__device__ __forceinline__ void merge_append_load(MergeAppend& ap, const AttnArgs& a, const MergeSpot& s) {
+  constexpr int SL = D / 8;
+  const int tok = a.merge_tok_is_row ? s.m : a.plan.merge_tok[s.m];
+  const int slot = a.plan.tok_slot[tok];
+  const int per = a.hkv * SL;  // chunks of K (or V) per token
 #pragma unroll
-    for (int i = 0; i < kAppendPerThread; ++i) {
-      const int e = qh * SL + sl + i * a.hq * SL;
-      if (e < 2 * per) {
-        const bool is_v = e >= per;
-        const int hh = (e % per) / SL, c = e % SL;
-        app_val[i] = *reinterpret_cast<const u32x4*>((is_v ? a.v_new : a.k_new) + (size_t(tok) * a.hkv + hh) * D + 8 * c);
-        app_dst[i] = const_cast<uint16_t*>(is_v ? a.vpool : a.kpool) +
-                     ((size_t(slot >> 4) * a.hkv + hh) * 16 + (slot & 15)) * D + 8 * c;
-      }
+  for (int i = 0; i < MergeAppend::kMost; ++i) {
+    const int e = s.qh * SL + s.sl + i * a.hq * SL;
+    if (e < 2 * per) {
+      const bool is_v = e >= per;
+      const int hh = (e % per) / SL, c = e % SL;
+      ap.val[i] = *reinterpret_cast<const u32x4*>((is_v ? a.v_new : a.k_new) + (size_t(tok) * a.hkv + hh) * D + 8 * c);
+      ap.dst[i] = const_cast<uint16_t*>(is_v ? a.vpool : a.kpool) +
+                  ((size_t(slot >> 4) * a.hkv + hh) * 16 + (slot & 15)) * D + 8 * c;
     }
   }
-  const size_t unit = size_t(m) * a.hkv + (qh >> a.group_shift);
+}
+
+__device__ __forceinline__ void merge_append_store(const MergeAppend& ap) {
+#pragma unroll
+  for (int i = 0; i < MergeAppend::kMost; ++i)
+    if (ap.dst[i]) *reinterpret_cast<u32x4*>(ap.dst[i]) = ap.val[i];
+}
+
+// The parts of a merge thread's row.
+struct MergeSource {
+  const uint16_t* op;  // unit 4 (blk / 2) + grp of the row in slot 0: blocks blk and blk + 1
+  const f32x2* lp;     // (m, l) of the row in slot 0
+  size_t stride;       // rows between slots
+  int nparts;
+};
+
+template <int D>
+__device__ __forceinline__ MergeSource merge_source(const AttnArgs& a, const MergeSpot& s) {
+  const size_t unit = size_t(s.m) * a.hkv + (s.qh >> a.group_shift);
   const MergeHead mh = a.merge_parts ? MergeHead{int32_t(unit) * a.merge_parts, a.merge_parts} : a.plan.merge_head[unit];
-  const int tok = F && a.merge_tok_is_row ? m : a.plan.merge_tok[m];
-  const size_t row0 = size_t(mh.base) * a.group + (qh & (a.group - 1));
-  const size_t stride = size_t(a.group);  // rows between slots
-  // Unit 4 (blk / 2) + grp of the row in slot 0: blocks blk and blk + 1.
-  const uint16_t* op =
-      part_unit0(a.plan.o_part, row0, qh & (a.group - 1), a.group, grp, D) + part_unit_stride(a.group) * (blk / 2);
-  const f32x2* lp = reinterpret_cast<const f32x2*>(a.plan.l_part) + row0;
+  const int g = s.qh & (a.group - 1);
+  const size_t row0 = size_t(mh.base) * a.group + g;
+  MergeSource r;
+  r.op = part_unit0(a.plan.o_part, row0, g, a.group, s.grp, D) + part_unit_stride(a.group) * (s.blk / 2);
+  r.lp = reinterpret_cast<const f32x2*>(a.plan.l_part) + row0;
+  r.stride = size_t(a.group);
+  r.nparts = mh.nparts;
+  return r;
+}
+
+// A merged state: running maximum, sum, and the values of the two blocks.
+struct MergeState {
+  float mx, z;
+  f32x4 acc0, acc1;
+};
+
+// Merge up to kMergeBatch parts, k0, k0 + step, ..., all requested before any
+// is used.  Part k weighs 2^(m_k - mx) l_k: its values are already divided by
+// l_k.
+template <int D>
+__device__ __forceinline__ MergeState merge_batch(const MergeSource& r, int k0, int step) {
   f32x2 ml[kMergeBatch];
   u32x4 ov[kMergeBatch];
 #pragma unroll
-  for (int k = 0; k < kMergeBatch; ++k) {
-    if (k < mh.nparts) {
-      ml[k] = lp[k * stride];
-      ov[k] = *reinterpret_cast<const u32x4*>(op + k * stride * D);
+  for (int i = 0; i < kMergeBatch; ++i) {
+    const int k = k0 + i * step;
+    if (k < r.nparts) {
+      ml[i] = r.lp[k * r.stride];
+      ov[i] = *reinterpret_cast<const u32x4*>(r.op + k * r.stride * D);
     } else {
-      ml[k] = f32x2{kNegBig, 0.f};
-      ov[k] = u32x4{0u, 0u, 0u, 0u};
+      ml[i] = f32x2{kNegBig, 0.f};
+      ov[i] = u32x4{0u, 0u, 0u, 0u};
     }
   }
-  float mx = kNegBig;
+  MergeState s = {kNegBig, 0.f, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-  for (int k = 0; k < kMergeBatch; ++k) mx = fmaxf(mx, ml[k][0]);
-  for (int k = kMergeBatch; k < mh.nparts; ++k) mx = fmaxf(mx, lp[k * stride][0]);
-  float z = 0.f;
-  f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-  // Part k weighs 2^(m_k - mx) l_k: its values are already divided by l_k.
+  for (int i = 0; i < kMergeBatch; ++i) s.mx = fmaxf(s.mx, ml[i][0]);
 #pragma unroll
-  for (int k = 0; k < kMergeBatch; ++k) {
-    const float wl = fast_exp2(ml[k][0] - mx) * ml[k][1];  // 0 for unused slots and for pieces that saw no key
-    z += wl;
-    acc0 += wl * unpack_bf16x4(ov[k][0], ov[k][1]);
-    acc1 += wl * unpack_bf16x4(ov[k][2], ov[k][3]);
+  for (int i = 0; i < kMergeBatch; ++i) {
+    const float wl = fast_exp2(ml[i][0] - s.mx) * ml[i][1];  // 0 for unused slots and for pieces that saw no key
+    s.z += wl;
+    s.acc0 += wl * unpack_bf16x4(ov[i][0], ov[i][1]);
+    s.acc1 += wl * unpack_bf16x4(ov[i][2], ov[i][3]);
   }
-  for (int k = kMergeBatch; k < mh.nparts; ++k) {
-    const f32x2 x = lp[k * stride];
-    const float wl = fast_exp2(x[0] - mx) * x[1];
-    const u32x4 v = *reinterpret_cast<const u32x4*>(op + k * stride * D);
-    z += wl;
-    acc0 += wl * unpack_bf16x4(v[0], v[1]);
-    acc1 += wl * unpack_bf16x4(v[2], v[3]);
-  }
-  const float inv = 1.0f / z;
-  uint16_t* out = a.o + (size_t(tok) * a.hq + qh) * D + 16 * blk + 4 * grp;
-  *reinterpret_cast<u32x2*>(out) = u32x2{pack_bf16(acc0[0] * inv, acc0[1] * inv), pack_bf16(acc0[2] * inv, acc0[3] * inv)};
+  return s;
+}
+
+// s with another merged state's parts added.
+__device__ __forceinline__ void merge_add(MergeState& s, const MergeState& x) {
+  const float mx = fmaxf(s.mx, x.mx);
+  const float f = fast_exp2(s.mx - mx), g = fast_exp2(x.mx - mx);
+  s.mx = mx;
+  s.z = s.z * f + x.z * g;
+  s.acc0 = s.acc0 * f + x.acc0 * g;
+  s.acc1 = s.acc1 * f + x.acc1 * g;
+}
+
+template <int D>
+__device__ __forceinline__ void merge_write(const AttnArgs& a, const MergeSpot& sp, int tok, const MergeState& s) {
+  const float inv = 1.0f / s.z;
+  uint16_t* out = a.o + (size_t(tok) * a.hq + sp.qh) * D + 16 * sp.blk + 4 * sp.grp;
+  *reinterpret_cast<u32x2*>(out) =
+      u32x2{pack_bf16(s.acc0[0] * inv, s.acc0[1] * inv), pack_bf16(s.acc0[2] * inv, s.acc0[3] * inv)};
   *reinterpret_cast<u32x2*>(out + 16) =
-      u32x2{pack_bf16(acc1[0] * inv, acc1[1] * inv), pack_bf16(acc1[2] * inv, acc1[3] * inv)};
-  if (a.lse && sl == 0) a.lse[size_t(tok) * a.hq + qh] = (mx + log2f(z)) * kLn2;
+      u32x2{pack_bf16(s.acc1[0] * inv, s.acc1[1] * inv), pack_bf16(s.acc1[2] * inv, s.acc1[3] * inv)};
+  if (a.lse && sp.sl == 0) a.lse[size_t(tok) * a.hq + sp.qh] = (s.mx + log2f(s.z)) * kLn2;
+}
+
+// Rows of at most kMergeBatch parts.  F: the append of this step is folded
+// in.  The decode launch read every decode token's new K/V straight from
+// k_new / v_new; the merge, which runs after it, writes them into their pool
+// slots (2 Hkv D / 8 chunks of 16 bytes per token, spread over the token's
+// threads).
+template <int D, bool F>
+__global__ __launch_bounds__(128) void merge_rows_kernel(AttnArgs a, int n_tok) {
+  const size_t t = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (t >= size_t(n_tok) * a.hq * (D / 8)) return;
+  const MergeSpot sp = merge_spot<D>(a, t);
+  MergeAppend ap;
+  if constexpr (F) merge_append_load<D>(ap, a, sp);
+  const MergeSource src = merge_source<D>(a, sp);
+  const int tok = F && a.merge_tok_is_row ? sp.m : a.plan.merge_tok[sp.m];
+  merge_write<D>(a, sp, tok, merge_batch<D>(src, 0, 1));
+  if constexpr (F) merge_append_store(ap);
+}
+
+// Rows of more parts: the four waves of a workgroup take every fourth part of
+// the same 64 units, kMergeBatch at a time, and meet in LDS.  A merge of few
+// rows is bound by its chain of loads: one thread taking a unit's parts in
+// turn past the first eight pays a round trip for each (one request, 2048 +
+// 288 keys, 8 heads: a step at 2-step pieces, 37 parts a row, 27.4 us, here
+// 11.8 us).  Up to eight parts one thread has them all in flight, and four
+// waves would only add the meeting.
+template <int D, bool F>
+__global__ __launch_bounds__(256) void merge_parts_kernel(AttnArgs a, int n_tok) {
+  __shared__ float meet[3][10][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const size_t t = size_t(blockIdx.x) * 64 + lane;
+  const bool live = t < size_t(n_tok) * a.hq * (D / 8);
+  const MergeSpot sp = merge_spot<D>(a, live ? t : 0);
+  MergeAppend ap;
   if constexpr (F) {
-#pragma unroll
-    for (int i = 0; i < kAppendPerThread; ++i)
-      if (app_dst[i]) *reinterpret_cast<u32x4*>(app_dst[i]) = app_val[i];
+    if (live && wave == 0) merge_append_load<D>(ap, a, sp);
   }
+  const MergeSource src = merge_source<D>(a, sp);
+  const int tok = a.plan.merge_tok[sp.m];
+  MergeState s = merge_batch<D>(src, wave, 4);
+  for (int k = wave + 4 * kMergeBatch; k < src.nparts; k += 4 * kMergeBatch) merge_add(s, merge_batch<D>(src, k, 4));
+  if (wave) {
+    float(*w)[64] = meet[wave - 1];
+    w[0][lane] = s.mx;
+    w[1][lane] = s.z;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      w[2 + e][lane] = s.acc0[e];
+      w[6 + e][lane] = s.acc1[e];
+    }
+  }
+  __syncthreads();
+  if (wave || !live) return;
+#pragma unroll
+  for (int x = 0; x < 3; ++x) {
+    MergeState o;
+    o.mx = meet[x][0][lane];
+    o.z = meet[x][1][lane];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      o.acc0[e] = meet[x][2 + e][lane];
+      o.acc1[e] = meet[x][6 + e][lane];
+    }
+    merge_add(s, o);
+  }
+  merge_write<D>(a, sp, tok, s);
+  if constexpr (F) merge_append_store(ap);
 }
 
 template <int D>
@@ -1630,19 +1739,19 @@ static int check_pool_matches(const pfx_pool* pool, const pfx_plan* p, const cha
   return PFX_OK;
 }
 
-// The decode launch alone: wide prefix blocks (if any) and the pieces.
+// The decode launch: extend or wide prefix blocks (a.num_wide of them from
+// a.wide_first) and the pieces.
 template <int D>
 static void launch_decode(const AttnArgs& a, const pfx_plan* p, hipStream_t s) {
-  const int S = std::min<int>(a.num_workers, p->num_segs);
-  const dim3 grid(p->num_wide + S);
+  const dim3 grid(a.num_wide + std::min<int>(a.num_workers, p->num_segs));
   if (p->decode_engine == PFX_DECODE_VALU) {
     if (a.fuse_append) hipLaunchKernelGGL((decode_kernel<D, true, false, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((decode_kernel<D, false, false, true>), grid, dim3(256), 0, s, a);
   } else if (a.fuse_append) {
-    if (p->num_wide) hipLaunchKernelGGL((decode_kernel<D, true, true, false>), grid, dim3(256), 0, s, a);
+    if (a.num_wide) hipLaunchKernelGGL((decode_kernel<D, true, true, false>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((decode_kernel<D, true, false, false>), grid, dim3(256), 0, s, a);
   } else {
-    if (p->num_wide) hipLaunchKernelGGL((decode_kernel<D, false, true, false>), grid, dim3(256), 0, s, a);
+    if (a.num_wide) hipLaunchKernelGGL((decode_kernel<D, false, true, false>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((decode_kernel<D, false, false, false>), grid, dim3(256), 0, s, a);
   }
 }
@@ -1658,23 +1767,30 @@ static void launch_all(AttnArgs a, const pfx_plan* p, hipStream_t s) {
     AttnArgs m = a;
     m.num_wide = p->num_items + p->num_wide;
     m.wide_first = 0;
-    const int S = std::min<int>(a.num_workers, p->num_segs);
-    hipLaunchKernelGGL((decode_kernel<D, false, true, false>), dim3(m.num_wide + S), dim3(256), 0, s, m);
+    launch_decode<D>(m, p, s);
   } else {
     if (p->num_items > 0) hipLaunchKernelGGL((extend_kernel<D>), dim3(p->num_items), dim3(256), 0, s, a);
     if (p->num_segs > 0 || p->num_wide > 0) launch_decode<D>(a, p, s);
   }
   const int n_tok = static_cast<int>(p->merge_tok.size());
   if (n_tok) {
-    // Workgroups of 128 threads: a decode-8B merge (32768 threads) then
-    // spreads over every compute unit instead of half of them.
-    constexpr int kMergeThreads = 128;
-    const size_t threads = size_t(n_tok) * p->hq * (D / 8);
-    const dim3 grid((threads + kMergeThreads - 1) / kMergeThreads);
-    if (a.fuse_append)
-      hipLaunchKernelGGL((merge_rows_kernel<D, true>), grid, dim3(kMergeThreads), 0, s, a, n_tok);
-    else
-      hipLaunchKernelGGL((merge_rows_kernel<D, false>), grid, dim3(kMergeThreads), 0, s, a, n_tok);
+    const size_t units = size_t(n_tok) * p->hq * (D / 8);
+    if (p->max_parts <= kMergeBatch) {
+      // Workgroups of 128 threads: a decode-8B merge (32768 threads) then
+      // spreads over every compute unit instead of half of them.
+      constexpr int kMergeThreads = 128;
+      const dim3 grid((units + kMergeThreads - 1) / kMergeThreads);
+      if (a.fuse_append)
+        hipLaunchKernelGGL((merge_rows_kernel<D, true>), grid, dim3(kMergeThreads), 0, s, a, n_tok);
+      else
+        hipLaunchKernelGGL((merge_rows_kernel<D, false>), grid, dim3(kMergeThreads), 0, s, a, n_tok);
+    } else {
+      const dim3 grid((units + 63) / 64);
+      if (a.fuse_append)
+        hipLaunchKernelGGL((merge_parts_kernel<D, true>), grid, dim3(256), 0, s, a, n_tok);
+      else
+        hipLaunchKernelGGL((merge_parts_kernel<D, false>), grid, dim3(256), 0, s, a, n_tok);
+    }
   }
 }
 

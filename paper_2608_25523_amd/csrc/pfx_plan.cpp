@@ -37,13 +37,33 @@ static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 static int64_t pages_for(int64_t tokens) { return (tokens + PFX_PAGE_SIZE - 1) / PFX_PAGE_SIZE; }
 
-// Longest decode piece by default, in steps: 16, or 64 once the decode
-// items hold at least kLongPiecesFrom steps.  Every piece costs a Q stage,
-// a partial state and its share of the merge; shorter pieces balance a
-// small launch better.
+// Longest decode piece by default, in steps.  Every piece costs a workgroup's
+// start, a Q stage, a partial state and its share of the merge; shorter
+// pieces balance a small launch better.  Measured with one layer's steps in
+// turn over 16 pools (nothing of K/V left in the last-level cache), Hq 32,
+// Hkv 8, d 128, us per step call.
+//   From kLongPiecesFrom steps on: 64.
+//   From kMidPiecesFrom on: 32.  100 requests of 4 agents (13464 steps) 51.9
+//   at 16, 49.4 at 32, 65.0 at 64; 160 of 8 (25408) 90.2, 85.8, 86.2; 64
+//   requests of 4 agents (7032) 30.0 at 16, 38.9 at 32.
+//   Below: the shortest from kLeastPieceSteps on with which the whole launch
+//   is resident at once, else 16.  A launch that size is bound by its longest
+//   workgroup, about 0.75 us a step after 4.5 us of start, not by memory, and
+//   one workgroup past the resident ones waits for a whole piece to end.  At
+//   16-step pieces and at this rule's (pieces): one request over 2048 + 288
+//   keys 18.6 -> 10.4 (3 steps, 200); 4 requests of one agent 19.2 -> 11.3 (3,
+//   280); 16 of three agents 20.4 -> 16.9 (7, 456); 32 of four 21.7 -> 20.1
+//   (11, 496).  Two steps a piece: 11.8 and 12.8 for the first two.  More
+//   workgroups than fit: 19.5 (6, 528) and 21.3 (6, 744) for the last two.
 constexpr int32_t kDefaultPieceSteps = 16;
+constexpr int32_t kMidPieceSteps = 32;
+constexpr int64_t kMidPiecesFrom = 12288;
 constexpr int32_t kLongPieceSteps = 64;
 constexpr int64_t kLongPiecesFrom = 32768;
+constexpr int32_t kLeastPieceSteps = 3;
+// Workgroups resident at once on 256 compute units, by the registers: two on
+// each at d = 128, four at d = 64.
+constexpr int64_t kResident128 = 512, kResident64 = 1024;
 
 DevPlan dev_plan(const pfx_plan* p, void* ws) {
   unsigned char* base = static_cast<unsigned char*>(ws);
@@ -311,6 +331,8 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     int32_t n = p->req[r].n;
     return n >= 1 && n * G <= kTileCols;
   };
+  const int32_t rows_per_block = kExtendTileCols / G;  // query rows of an extend block
+  auto extend_blocks = [&](int32_t r) { return (p->req[r].n + rows_per_block - 1) / rows_per_block; };
   auto blocks_for = [&](int32_t tokens) { return (tokens * G + kTileCols - 1) / kTileCols; };
 
   // ---- decode items (Sec. 3): each agent's prefix once per block of its
@@ -381,21 +403,31 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     int32_t item, piece, s0, s1;
   };
   std::vector<Piece> pcs;
+  auto item_steps = [](const DItem& x) { return (x.keys + kStepKeys - 1) / kStepKeys; };
   if (piece_steps == 0) {
     int64_t steps = 0;
-    for (const DItem& x : dit) steps += (x.keys + kStepKeys - 1) / kStepKeys;
-    piece_steps = steps >= kLongPiecesFrom ? kLongPieceSteps : kDefaultPieceSteps;
+    for (const DItem& x : dit) steps += item_steps(x);
+    piece_steps = steps >= kLongPiecesFrom  ? kLongPieceSteps
+                  : steps >= kMidPiecesFrom ? kMidPieceSteps
+                                            : kDefaultPieceSteps;
+    // Workgroups left for the pieces beside the extend blocks.
+    int64_t room = p->d == 128 ? kResident128 : kResident64;
+    for (int32_t r = 0; r < R && room > 0; ++r)
+      if (p->req[r].n > 0 && !is_decode_class(r)) room -= int64_t(hkv) * extend_blocks(r);
+    if (room > 0 && int64_t(dit.size()) <= room)
+      for (int64_t l = std::max<int64_t>(kLeastPieceSteps, (steps + room - 1) / room); l < piece_steps; ++l) {
+        int64_t pieces = 0;
+        for (const DItem& x : dit) pieces += (item_steps(x) + l - 1) / l;
+        if (pieces <= room) piece_steps = static_cast<int32_t>(l);
+      }
   }
   {
     size_t total = 0;
-    for (const DItem& x : dit) {
-      const int32_t ns = (x.keys + kStepKeys - 1) / kStepKeys;
-      total += size_t((ns + piece_steps - 1) / piece_steps);
-    }
+    for (const DItem& x : dit) total += size_t((item_steps(x) + piece_steps - 1) / piece_steps);
     pcs.reserve(total);
   }
   for (size_t xi = 0; xi < dit.size(); ++xi) {
-    const int32_t ns = (dit[xi].keys + kStepKeys - 1) / kStepKeys;
+    const int32_t ns = item_steps(dit[xi]);
     const int32_t np = (ns + piece_steps - 1) / piece_steps;
     p->num_decode_steps += ns;
     for (int32_t k = 0; k < np; ++k)
@@ -443,6 +475,7 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   // slots start at (row * Hkv + h) * P, and the merge launch computes that
   // instead of loading merge_head (one dependent round trip less).
   p->merge_parts = 0;
+  for (const MergeHead& mh : p->merge_head) p->max_parts = std::max(p->max_parts, mh.nparts);
   if (!p->merge_head.empty()) {
     const int32_t P = p->merge_head[0].nparts;
     bool uniform = P >= 1;
@@ -549,9 +582,8 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     const int32_t a = b->agent[r];
     const int32_t P = a >= 0 ? pt->prefix_len[a] : 0;
     const int32_t L = b->suffix_len[r];
-    const int32_t per = kExtendTileCols / G;
-    for (int32_t i0 = 0; i0 < ri.n; i0 += per) {
-      const int32_t i1 = std::min(ri.n, i0 + per);
+    for (int32_t i0 = 0; i0 < ri.n; i0 += rows_per_block) {
+      const int32_t i1 = std::min(ri.n, i0 + rows_per_block);
       const int32_t rbeg = static_cast<int32_t>(p->row_tok.size());
       for (int32_t i = i0; i < i1; ++i) p->row_tok.push_back(ri.q_start + i);
       xbs.push_back(XBlock{r, i0, i1, rbeg, int64_t(P) + (L - ri.n + i1)});

@@ -1,0 +1,45 @@
+"""The merge launches at the edges of their part counts, on the GPU: rows of
+1 and of 8 parts (one thread per unit), 9 (the first count that four waves
+share), 32 and 33 (one and two batches of a wave's parts) and 66."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2608_25523_amd import binding as B  # noqa: E402
+from paper_2608_25523_amd import runner as RN  # noqa: E402
+from paper_2608_25523_amd import workloads as W  # noqa: E402
+from test_gpu_parity import announce, assert_untouched, run_and_check  # noqa: E402
+import parity as PT  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(128, 32, 8), (64, 6, 3)])
+@pytest.mark.parametrize("parts", [1, 8, 9, 32, 33, 66])
+def test_merge_part_counts(parts, d, hq, hkv):
+    """One-step pieces: a request over parts - 1 prefix steps and one suffix
+    step has `parts` parts, one without a prefix as many suffix steps, and a
+    row of few parts sits beside them.  Against the oracle, and pfx_step
+    (append folded into the merge) against append + attention bit for bit."""
+    plen = 32 * (parts - 1)
+    b = W.make_batch(300 + parts, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=512,
+                     prefix_len=[plen, 20], agent=[0, -1, 1, 0], suffix_len=[7, 32 * parts - 5, 3, 32],
+                     n_rows=[1, 1, 2, 1])
+    hv = W.host_values(b, 400 + parts)
+    ds, o_ref, l_ref = run_and_check(b, hv, f"merge-parts-{parts}-d{d}", piece_steps=1)
+    assert int(ds.plan.export(7)[:, 1].max()) == max(parts, 2)
+    del ds
+    ds = RN.DeviceStep(b, hv, piece_steps=1)
+    B.pfx_step(ds.pool, ds.plan, ds.k_new, ds.v_new, ds.q, ds.o, ds.lse)
+    B.pfx_sync_check()
+    o, l = ds.outputs()
+    assert np.array_equal(o, o_ref) and np.array_equal(l, l_ref)
+    exp_k, exp_v = PT.expected_pools(b, hv)
+    gk, gv = ds.read_pages(hv.pages)
+    assert np.array_equal(gk, exp_k) and np.array_equal(gv, exp_v)
+    assert_untouched(ds, hv.pages, "merge-parts step")
+    announce(f"merge parts {parts} d={d}: step equals append + attention")

@@ -1,0 +1,49 @@
+"""The default decode piece length (host only): the shortest from 3 steps on
+with which every workgroup of the launch is resident at once, 16 where none
+is, 32 from 12288 steps on."""
+
+import numpy as np
+import pytest
+
+pytest.importorskip("torch")
+
+from paper_2608_25523_amd import binding as B  # noqa: E402
+from paper_2608_25523_amd import workloads as W  # noqa: E402
+
+
+def plan(b, **kw):
+    return B.plan_from_batch(B.make_pool(b.num_pages, b.num_kv_heads, b.head_dim), b, B.PFX_MODE_MIXED, **kw)
+
+
+def batch(d, reqs, plen, extend=0):
+    a = np.arange(reqs + (extend > 0)) % len(plen)
+    n = [1] * reqs + ([extend] if extend else [])
+    s = [33 + 37 * i % 500 for i in range(reqs)] + ([extend] if extend else [])
+    return W.make_batch(7, num_q_heads=32, num_kv_heads=8, head_dim=d, num_pages=65536, prefix_len=plen, agent=a,
+                        suffix_len=s, n_rows=n)
+
+
+@pytest.mark.parametrize("d,reqs,plen,extend", [
+    (128, 1, [2048], 0), (128, 4, [2048], 0), (128, 16, [700, 3000, 1500], 0), (128, 32, [500, 3000], 0),
+    (64, 32, [500, 3000], 0), (128, 64, [2048] * 4, 0), (128, 4, [2048], 600), (128, 4, [2048], 3000),
+    (128, 1, [], 0)])
+def test_shortest_length_that_is_resident(d, reqs, plen, extend):
+    if not plen:
+        b = W.make_batch(7, num_q_heads=32, num_kv_heads=8, head_dim=d, num_pages=64, prefix_len=[], agent=[-1],
+                         suffix_len=[20], n_rows=[1])
+    else:
+        b = batch(d, reqs, plen, extend)
+    s = plan(b).stats()
+    assert s.num_decode_steps < 12288
+    room = (512 if d == 128 else 1024) - s.num_extend_items
+    count = {l: plan(b, piece_steps=l).stats() for l in range(3, 17)}
+    fits = [l for l in count if count[l].num_decode_pieces + count[l].num_wide_blocks <= room]
+    want = count[min(fits) if fits else 16]
+    assert (s.num_decode_pieces, s.num_wide_blocks) == (want.num_decode_pieces, want.num_wide_blocks)
+
+
+def test_length_of_larger_launches():
+    b = batch(128, 160, [500, 4000, 2000, 1000])
+    s = plan(b).stats()
+    assert 12288 <= s.num_decode_steps < 32768
+    assert s.num_decode_pieces == plan(b, piece_steps=32).stats().num_decode_pieces
