@@ -59,6 +59,28 @@ struct alignas(16) Item {
 };
 static_assert(sizeof(Item) == 128, "Item is 32 int32");
 
+// A piece of an extend block: steps [st0, st1) of the block's step sequence
+// (its prefix steps, then its suffix steps), st0 even.  pages: the page ids of
+// steps st0 and st0 + 1, two each, so that they can be requested before the
+// page list arrives.  slot: where its state goes, or -1 when it is the whole
+// block and writes final rows.
+struct alignas(16) Chunk {
+  int32_t item;
+  int32_t st0, st1;
+  int32_t slot;
+  int32_t pages[4];
+};
+static_assert(sizeof(Chunk) == 32, "Chunk is 8 int32");
+
+// An extend block that was cut: its nparts states are in slots base,
+// base + 1, ...  A slot holds, in fp32, the block's unnormalised accumulators
+// as the four waves' lanes hold them (32 columns a wave: [wave][16-column
+// block][dims 16 blk ..][lane] f32x4, 128 D floats) and the pair (m, l) of
+// each of its 128 columns.
+struct ChunkMerge {
+  int32_t item, base, nparts, pad;
+};
+
 // Decode work.  A decode item is one KV head's whole key range for a set of
 // query rows: an agent's prefix against a block of its decode rows (<= 64
 // columns), or one request's suffix against its own rows.  Items are cut
@@ -119,8 +141,12 @@ struct DevPlan {
   const Seg* segs;              // decode pieces, longest first
   const int32_t* merge_tok;     // decode tokens (their rows are merged from pieces)
   const MergeHead* merge_head;  // [merge token][KV head]
+  const Chunk* chunks;          // pieces of the extend blocks, when some are cut
+  const ChunkMerge* chunk_merge;
   uint16_t* o_part;             // [partial row][d] bf16, in the partial layout
   float* l_part;                // [partial row][2]
+  float* xo_part;               // [chunk slot][128 D]
+  float* xl_part;               // [chunk slot][128 columns][2]
 };
 
 // Per-request bookkeeping (host).
@@ -140,6 +166,8 @@ struct pfx_plan {
   int32_t num_wide = 0;        // wide prefix blocks, after the extend blocks in the same array
   std::vector<int32_t> row_tok, row_out, page_list, tok_req, tok_slot;
   std::vector<pfx::ReqInfo> req;
+  int32_t num_chunks = 0;      // pieces of the extend blocks (0: none is cut, one workgroup per block)
+  int32_t num_chunk_merges = 0;  // extend blocks that are cut
   int32_t num_segs = 0;        // decode pieces (their records live in the blob at off_segs)
   int32_t merge_parts = 0;     // P when every merged (row, KV head) has P parts at slots (row * Hkv + h) * P, else 0
   int32_t max_parts = 0;         // most parts of a merged (row, KV head)
@@ -152,7 +180,8 @@ struct pfx_plan {
   int32_t pages_needed = 0;
   // byte offsets inside the workspace
   size_t off_items = 0, off_row_tok = 0, off_row_out = 0, off_page_list = 0, off_tok_slot = 0, off_segs = 0,
-         off_merge_tok = 0, off_merge_head = 0, off_opart = 0, off_lpart = 0, total_bytes = 0, blob_bytes = 0;
+         off_merge_tok = 0, off_merge_head = 0, off_opart = 0, off_lpart = 0, off_chunks = 0, off_chunk_merge = 0, off_xopart = 0, off_xlpart = 0,
+         total_bytes = 0, blob_bytes = 0;
   std::vector<unsigned char> blob;  // host image of [0, blob_bytes)
   const pfx::Item* host_items() const { return reinterpret_cast<const pfx::Item*>(blob.data() + off_items); }
   const pfx::Seg* host_segs() const { return reinterpret_cast<const pfx::Seg*>(blob.data() + off_segs); }

@@ -12,12 +12,14 @@
 // V^T is read from the LDS stage with ds_read_b64_tr_b16, which hands each
 // lane 4 keys of one head dim out of a key-major tile.
 //
-// Up to three launches per call, in stream order (a batch with both extend
+// Up to four launches per call, in stream order (a batch with both extend
 // blocks and decode pieces runs the first two as one launch, the extend
 // blocks leading its grid):
 //   extend blocks: one workgroup per block of <= 128 query columns of one
 //     request and one KV head, streaming the prefix and the causal suffix
-//     through an LDS ring; rows written directly.
+//     through an LDS ring; rows written directly.  In a launch too small to
+//     fill the chip the blocks are cut along their keys into pieces that
+//     leave fp32 states, which a launch of their own merges.
 //   decode: one workgroup per piece, or persistent ones.  The decode items (an agent's prefix
 //     against a block of its decode rows, a request's suffix against its own
 //     rows; one KV head each) are cut into pieces of at most 64 32-key
@@ -161,9 +163,10 @@ struct AttnArgs {
   const uint16_t* k_new;
   const uint16_t* v_new;
   int32_t fuse_append;
-  // Decode launch: its first num_wide workgroups run the wide prefix blocks
-  // items[wide_first ...], the others the decode pieces.
-  int32_t num_wide, wide_first;
+  // Decode launch: its first num_wide workgroups run num_chunks pieces of
+  // extend blocks (mixed_chunk_kernel), then the blocks items[wide_first ...] (extend or wide
+  // prefix blocks), the others the decode pieces.
+  int32_t num_wide, wide_first, num_chunks;
   // Merge launch: P when every (merge row m, KV head h) has P parts from
   // slot (m Hkv + h) P (then merge_head is not read), else 0; and 1 when
   // merge row m is token m for every m (then the merge with the append
@@ -1043,14 +1046,19 @@ constexpr int extend_smem_bytes() { return kStages * TileGeom<D>::stage_bytes; }
 // for its own copies, all waves meet (the pair's stages complete everywhere,
 // the previous pair's stages consumed), those are refilled two steps ahead,
 // and every wave multiplies the pair against its own columns.
-template <int D, int QBW>
-__device__ __forceinline__ void extend_block(const AttnArgs& a, const Item* itp, unsigned char* smem) {
+// C: the workgroup runs only the steps of a piece of the block (*ck) and
+// leaves its state in the piece's slot.
+template <int D, int QBW, bool C = false>
+__device__ __forceinline__ void extend_block(const AttnArgs& a, const Item* itp, unsigned char* smem,
+                                             const Chunk* ckp = nullptr) {
   using TG = TileGeom<D>;
   constexpr int KS = D / 32;
   constexpr int NS = kStages;
   auto ring = reinterpret_cast<unsigned char (*)[TG::stage_bytes]>(smem);
-  const int lead = itp->first_pages[threadIdx.x & (kItemPages - 1)];  // issued before the block's scalar load
+  // Issued before the block's scalar load.
+  const int lead = C ? ckp->pages[threadIdx.x & 3] : itp->first_pages[threadIdx.x & (kItemPages - 1)];
   const Item it = *itp;
+  const int first = C ? ckp->st0 : 0;  // the workgroup's first step
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int col = lane & 15, grp = lane >> 4;
@@ -1070,8 +1078,13 @@ __device__ __forceinline__ void extend_block(const AttnArgs& a, const Item* itp,
   pw.p0n = p0n;
   pw.ntab = p0n + p1n;
   pw.w0 = 0;
-  pw.cur = window_entry(pw, lane);
-  pw.next = window_entry(pw, 64 + lane);
+  if constexpr (C) {
+    // The window of step first + 2, the first one that is looked up.
+    const int s0_steps = (it.s0_kend - it.s0_kbeg + kStepKeys - 1) / kStepKeys;
+    pw.w0 = (2 * (first + 2) + (first + 2 >= s0_steps ? p0n - 2 * s0_steps : 0)) & ~63;
+  }
+  pw.cur = window_entry(pw, pw.w0 + lane);
+  pw.next = window_entry(pw, pw.w0 + 64 + lane);
 
   // This wave's query columns: blocks wave*QBW .. wave*QBW + QBW - 1.
   const int ncols = it.row_count * G;
@@ -1106,14 +1119,16 @@ __device__ __forceinline__ void extend_block(const AttnArgs& a, const Item* itp,
   WaveState<D, QBW> ws;
   reset_state(ws);
   const StepMarks mk = step_marks(it, p0n, lim_lo);
-  const int nsteps = mk.nsteps;
+  const int nsteps = C ? ckp->st1 : mk.nsteps;
   uint32_t voff[TG::loads_per_wave];
   block_lane_offsets<D>(voff, lane);
   // The first two steps' pages are among the leading ids (they travel in
   // the block record, one per lane): request them before the page windows
   // arrive.
-  for (int st = 0; st < 2 && st < nsteps; ++st)
-    issue_block_copy<D>(ring[st], a, __builtin_amdgcn_readfirstlane(__builtin_amdgcn_readlane(lead, step_entry(mk, st, wave))),
+  for (int i = 0; i < 2 && first + i < nsteps; ++i)
+    issue_block_copy<D>(ring[i], a,
+                        __builtin_amdgcn_readfirstlane(__builtin_amdgcn_readlane(
+                            lead, C ? 2 * i + (wave & 1) : step_entry(mk, i, wave))),
                         h, wave, voff);
   // Two steps per barrier: at pair q (steps 2q, 2q + 1) wait for both
   // stages, meet (so the stages of the previous pair are free), refill them
@@ -1121,7 +1136,7 @@ __device__ __forceinline__ void extend_block(const AttnArgs& a, const Item* itp,
   // so every copy of the body works on fixed stages and its LDS addresses
   // are a lane offset plus an immediate.
   static_assert(NS == 4, "pairs of steps in a ring of four stages");
-  for (int st0 = 0; st0 < nsteps; st0 += 4) {
+  for (int st0 = first; st0 < nsteps; st0 += 4) {
 #pragma unroll
     for (int k = 0; k < 2; ++k) {
       const int st = st0 + 2 * k;
@@ -1138,6 +1153,25 @@ __device__ __forceinline__ void extend_block(const AttnArgs& a, const Item* itp,
       // An odd last step pairs with an empty one (its stage is not being
       // refilled).
       if (nb > 0) extend_pair<D, QBW>(ws, ring[2 * k], ring[2 * k + 1], qf, lim, it, st, two, mk, lane, a.scale_log2);
+    }
+  }
+  if constexpr (C) {
+    const int slot = ckp->slot;
+    if (slot >= 0) {
+      // The piece's state as it stands, in fp32 as a block holds it.
+#pragma unroll
+      for (int b = 0; b < QBW; ++b) {
+        if (b >= nb) break;
+        float* out = a.plan.xo_part + size_t(slot) * (kExtendTileCols * D) + (wave * QBW + b) * (kTileCols * D) + 4 * lane;
+#pragma unroll
+        for (int blk = 0; blk < D / 16; ++blk)
+          __builtin_nontemporal_store(ws.acc[b][blk], reinterpret_cast<f32x4*>(out + 256 * blk));
+        const float l = column_sum(ws.lv[b][0]);
+        if (grp == 0)
+          reinterpret_cast<f32x2*>(a.plan.xl_part)[size_t(slot) * kExtendTileCols + (wave * QBW + b) * kTileCols + col] =
+              f32x2{ws.m[b], l};
+      }
+      return;
     }
   }
 #pragma unroll
@@ -1162,6 +1196,70 @@ template <int D>
 __global__ __launch_bounds__(256, 2) void extend_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[extend_smem_bytes<D>()];
   extend_block<D, 2>(a, a.plan.items + blockIdx.x, smem);
+}
+
+// Pieces of extend blocks.  A launch of few blocks is bound by the steps of one
+// block in series (300 rows over 4096 keys, Hq 32, Hkv 8, d 128: 80 blocks of
+// 69 pairs on 256 compute units, 92 us a step call with the append; as 480
+// pieces 39 us, of which the pieces take about 24 and their merge 8).
+template <int D>
+__global__ __launch_bounds__(256, 2) void extend_chunk_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[extend_smem_bytes<D>()];
+  const Chunk* ck = a.plan.chunks + blockIdx.x;
+  extend_block<D, 2, true>(a, a.plan.items + ck->item, smem, ck);
+}
+
+// The cut blocks' rows from their pieces' states: one thread per f32x4 of a
+// block's accumulators, reading it from every piece as it was stored.
+constexpr int kChunkMergeBatch = 4;
+
+template <int D>
+__global__ __launch_bounds__(256) void chunk_merge_kernel(AttnArgs a) {
+  constexpr int CH = D / 16;
+  constexpr int kPerItem = kExtendTileCols * D / 4 / 256;  // workgroups per block
+  const ChunkMerge cm = a.plan.chunk_merge[blockIdx.x / kPerItem];
+  const int u = (blockIdx.x % kPerItem) * 256 + threadIdx.x;
+  const int lane = u & 63, blk = (u >> 6) % CH, grp = lane >> 4;
+  const int c = (u >> 6) / CH * kTileCols + (lane & 15);
+  const Item* it = a.plan.items + cm.item;
+  const int j = c >> a.group_shift;
+  if (j >= it->row_count) return;
+  const float* op = a.plan.xo_part + size_t(cm.base) * (kExtendTileCols * D) + 4 * u;
+  const f32x2* lp = reinterpret_cast<const f32x2*>(a.plan.xl_part) + size_t(cm.base) * kExtendTileCols + c;
+  float mx = kNegBig, z = 0.f;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  for (int k0 = 0; k0 < cm.nparts; k0 += kChunkMergeBatch) {
+    f32x2 ml[kChunkMergeBatch];
+    f32x4 ov[kChunkMergeBatch];
+#pragma unroll
+    for (int i = 0; i < kChunkMergeBatch; ++i) {
+      if (k0 + i < cm.nparts) {
+        ml[i] = lp[size_t(k0 + i) * kExtendTileCols];
+        ov[i] = *reinterpret_cast<const f32x4*>(op + size_t(k0 + i) * (kExtendTileCols * D));
+      } else {
+        ml[i] = f32x2{kNegBig, 0.f};
+        ov[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+    }
+    float m2 = mx;
+#pragma unroll
+    for (int i = 0; i < kChunkMergeBatch; ++i) m2 = fmaxf(m2, ml[i][0]);
+    const float f = fast_exp2(mx - m2);
+    mx = m2;
+    z *= f;
+    acc *= f;
+#pragma unroll
+    for (int i = 0; i < kChunkMergeBatch; ++i) {
+      const float w = fast_exp2(ml[i][0] - mx);
+      z += w * ml[i][1];
+      acc += w * ov[i];
+    }
+  }
+  const int orow = (it->tok0 + j) * a.hq + it->kv_head * a.group + (c & (a.group - 1));
+  const float inv = z > 0.f ? 1.0f / z : 0.f;
+  *reinterpret_cast<u32x2*>(a.o + size_t(orow) * D + 16 * blk + 4 * grp) =
+      u32x2{pack_bf16(acc[0] * inv, acc[1] * inv), pack_bf16(acc[2] * inv, acc[3] * inv)};
+  if (a.lse && blk == 0 && grp == 0) a.lse[orow] = z > 0.f ? (mx + log2f(z)) * kLn2 : -INFINITY;
 }
 
 // ---------------------------------------------------------------------------
@@ -1262,8 +1360,9 @@ __device__ __forceinline__ int issue_piece_stage(unsigned char* stage, const Att
 
 // F: the append is folded in.  W: the launch starts with wide prefix blocks.
 // V: the pieces run on the vector ALU (no wide blocks then).
-template <int D, bool F, bool W, bool V>
-__global__ __launch_bounds__(256, 2) void decode_kernel(AttnArgs a) {
+// C: before those, pieces of extend blocks.
+template <int D, bool F, bool W, bool V, bool C>
+__device__ __forceinline__ void decode_workgroup(const AttnArgs& a, unsigned char* smem) {
   static_assert(!(V && W), "wide blocks run on the matrix unit");
   using TG = TileGeom<D>;
   constexpr int KS = D / 32;
@@ -1272,14 +1371,18 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(AttnArgs a) {
   constexpr int K = kPieceSlots;
   constexpr int kVecs = int(sizeof(Seg)) / 16;
   static_assert(kVecs > 64 && kVecs <= 128, "a descriptor is two copy instructions");
-  // Wide prefix blocks run the extend block's four-stage ring in the same bytes.
-  constexpr int kSmem = W ? std::max(extend_smem_bytes<D>(), decode_smem_bytes<D, V>()) : decode_smem_bytes<D, V>();
-  __shared__ __attribute__((aligned(1024))) unsigned char smem[kSmem];
+  if constexpr (C) {
+    if (int(blockIdx.x) < a.num_chunks) {
+      const Chunk* ck = a.plan.chunks + blockIdx.x;
+      extend_block<D, 2, true>(a, a.plan.items + ck->item, smem, ck);
+      return;
+    }
+  }
   if constexpr (W) {
     if (int(blockIdx.x) < a.num_wide) {
       // A wide prefix block: 128 decode columns against one piece of their
       // agent's prefix, the extend block's two-steps-per-barrier pipeline.
-      extend_block<D, 2>(a, a.plan.items + a.wide_first + blockIdx.x, smem);
+      extend_block<D, 2>(a, a.plan.items + a.wide_first + (blockIdx.x - (C ? a.num_chunks : 0)), smem);
       return;
     }
   }
@@ -1461,6 +1564,28 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(AttnArgs a) {
       }
     }
   }
+}
+
+// Wide prefix blocks and extend pieces run the extend block's four-stage ring
+// in the same bytes as the pieces' ring.
+template <int D, bool W, bool V>
+constexpr int decode_kernel_smem() {
+  return W ? std::max(extend_smem_bytes<D>(), decode_smem_bytes<D, V>()) : decode_smem_bytes<D, V>();
+}
+
+template <int D, bool F, bool W, bool V>
+__global__ __launch_bounds__(256, 2) void decode_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[decode_kernel_smem<D, W, V>()];
+  decode_workgroup<D, F, W, V, false>(a, smem);
+}
+
+// A mixed batch whose extend blocks are cut.  A kernel of its own: with the
+// pieces' code in decode_kernel, a batch of 32 large prefills and 448 decode
+// requests ran 1.5% slower.
+template <int D>
+__global__ __launch_bounds__(256, 2) void mixed_chunk_kernel(AttnArgs a) {
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[decode_kernel_smem<D, true, false>()];
+  decode_workgroup<D, false, true, false, true>(a, smem);
 }
 
 // Decode rows: the log-sum-exp merge of the pieces' states (softmax over a
@@ -1744,7 +1869,9 @@ static int check_pool_matches(const pfx_pool* pool, const pfx_plan* p, const cha
 template <int D>
 static void launch_decode(const AttnArgs& a, const pfx_plan* p, hipStream_t s) {
   const dim3 grid(a.num_wide + std::min<int>(a.num_workers, p->num_segs));
-  if (p->decode_engine == PFX_DECODE_VALU) {
+  if (a.num_chunks) {
+    hipLaunchKernelGGL((mixed_chunk_kernel<D>), grid, dim3(256), 0, s, a);
+  } else if (p->decode_engine == PFX_DECODE_VALU) {
     if (a.fuse_append) hipLaunchKernelGGL((decode_kernel<D, true, false, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((decode_kernel<D, false, false, true>), grid, dim3(256), 0, s, a);
   } else if (a.fuse_append) {
@@ -1759,18 +1886,24 @@ static void launch_decode(const AttnArgs& a, const pfx_plan* p, hipStream_t s) {
 template <int D>
 static void launch_all(AttnArgs a, const pfx_plan* p, hipStream_t s) {
   if (p->num_items > 0 && p->num_segs > 0 && p->decode_engine == PFX_DECODE_MFMA && !a.fuse_append) {
-    // A mixed batch in one launch: the extend blocks and the wide prefix
-    // blocks lead the grid (the same block routine as the extend launch, at
-    // the same block indices, so their XCD grouping holds), and the decode
-    // pieces follow, taking compute units as the extend blocks retire
-    // instead of waiting for the last of them.
+    // A mixed batch in one launch: the extend blocks (or their pieces) and
+    // the wide prefix blocks lead the grid (the same block routine as the
+    // extend launch, at the same block indices, so their XCD grouping holds),
+    // and the decode pieces follow, taking compute units as the extend blocks
+    // retire instead of waiting for the last of them.
     AttnArgs m = a;
-    m.num_wide = p->num_items + p->num_wide;
-    m.wide_first = 0;
+    m.num_chunks = p->num_chunks;
+    m.num_wide = (p->num_chunks ? p->num_chunks : p->num_items) + p->num_wide;
+    m.wide_first = p->num_chunks ? p->num_items : 0;
     launch_decode<D>(m, p, s);
   } else {
-    if (p->num_items > 0) hipLaunchKernelGGL((extend_kernel<D>), dim3(p->num_items), dim3(256), 0, s, a);
+    if (p->num_chunks) hipLaunchKernelGGL((extend_chunk_kernel<D>), dim3(p->num_chunks), dim3(256), 0, s, a);
+    else if (p->num_items > 0) hipLaunchKernelGGL((extend_kernel<D>), dim3(p->num_items), dim3(256), 0, s, a);
     if (p->num_segs > 0 || p->num_wide > 0) launch_decode<D>(a, p, s);
+  }
+  if (p->num_chunk_merges) {
+    const dim3 grid(p->num_chunk_merges * (kExtendTileCols * D / 4 / 256));
+    hipLaunchKernelGGL((chunk_merge_kernel<D>), grid, dim3(256), 0, s, a);
   }
   const int n_tok = static_cast<int>(p->merge_tok.size());
   if (n_tok) {
@@ -1856,6 +1989,7 @@ static int launch_attention(const pfx_pool* pool, const pfx_plan* p, const DevPl
   a.num_workers = p->decode_workers > 0 ? p->decode_workers : p->num_segs;
   a.num_wide = p->num_wide;
   a.wide_first = p->num_items;
+  a.num_chunks = 0;
   a.merge_parts = p->merge_parts;
   a.merge_tok_is_row = p->merge_tok_is_row;
   if (p->d == 128) launch_all<128>(a, p, s); else launch_all<64>(a, p, s);

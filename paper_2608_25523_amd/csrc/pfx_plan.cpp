@@ -65,6 +65,29 @@ constexpr int32_t kLeastPieceSteps = 3;
 // each at d = 128, four at d = 64.
 constexpr int64_t kResident128 = 512, kResident64 = 1024;
 
+// An extend launch of fewer blocks than fit the chip at once (512 workgroups,
+// two on a compute unit) may cut its blocks along their keys.  The launch is
+// then shorter, but every piece writes its state (66 KB at d = 128) and a
+// second launch reads them back.  What either takes, in pairs of steps of a
+// workgroup that shares its compute unit (1.9 us at d = 128, 1.2 at d = 64):
+//   uncut: the longest block, `alone` of it where its workgroup has the
+//     compute unit for itself;
+//   cut: the longest piece (likewise), `fixed` for the second launch, `slot`
+//     for every piece's state, `late` when decode pieces of the batch (16
+//     steps, 16 us) have to wait for them.
+// The blocks are cut when that saves a tenth.  Measured, us a step call uncut
+// and cut, Hq 32, Hkv 8, d 128: 300 rows over 4096 keys (80 blocks of 69
+// pairs) 92 and 39; 32 rows over 4096 (8 of 65) 86 and 21; 700 over 8192 (176
+// of 139) 178 and 128; 1000 over 4096 (256 of 80) 107 and 90; left uncut: 1999
+// over 2048 (504 of 64) 110 and 115, 8 requests of 30 to 100 over 1000 (176 of
+// 18) 31.5 and 32.7.
+constexpr int64_t kResidentExtend = 512, kComputeUnits = 256;
+constexpr int32_t kLeastChunkPairs = 4;
+struct ChunkCosts {
+  double alone, fixed, slot, late;
+};
+constexpr ChunkCosts kChunkCosts128 = {0.7, 4.5, 0.009, 8.5}, kChunkCosts64 = {0.9, 7.0, 0.006, 10.0};
+
 DevPlan dev_plan(const pfx_plan* p, void* ws) {
   unsigned char* base = static_cast<unsigned char*>(ws);
   DevPlan d;
@@ -78,6 +101,10 @@ DevPlan dev_plan(const pfx_plan* p, void* ws) {
   d.merge_head = reinterpret_cast<const MergeHead*>(base + p->off_merge_head);
   d.o_part = reinterpret_cast<uint16_t*>(base + p->off_opart);
   d.l_part = reinterpret_cast<float*>(base + p->off_lpart);
+  d.chunks = reinterpret_cast<const Chunk*>(base + p->off_chunks);
+  d.chunk_merge = reinterpret_cast<const ChunkMerge*>(base + p->off_chunk_merge);
+  d.xo_part = reinterpret_cast<float*>(base + p->off_xopart);
+  d.xl_part = reinterpret_cast<float*>(base + p->off_xlpart);
   return d;
 }
 
@@ -332,7 +359,6 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     return n >= 1 && n * G <= kTileCols;
   };
   const int32_t rows_per_block = kExtendTileCols / G;  // query rows of an extend block
-  auto extend_blocks = [&](int32_t r) { return (p->req[r].n + rows_per_block - 1) / rows_per_block; };
   auto blocks_for = [&](int32_t tokens) { return (tokens * G + kTileCols - 1) / kTileCols; };
 
   // ---- decode items (Sec. 3): each agent's prefix once per block of its
@@ -410,10 +436,10 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     piece_steps = steps >= kLongPiecesFrom  ? kLongPieceSteps
                   : steps >= kMidPiecesFrom ? kMidPieceSteps
                                             : kDefaultPieceSteps;
-    // Workgroups left for the pieces beside the extend blocks.
     int64_t room = p->d == 128 ? kResident128 : kResident64;
+    // Beside extend blocks, which take longer, the pieces stay long.
     for (int32_t r = 0; r < R && room > 0; ++r)
-      if (p->req[r].n > 0 && !is_decode_class(r)) room -= int64_t(hkv) * extend_blocks(r);
+      if (p->req[r].n > 0 && !is_decode_class(r)) room = 0;
     if (room > 0 && int64_t(dit.size()) <= room)
       for (int64_t l = std::max<int64_t>(kLeastPieceSteps, (steps + room - 1) / room); l < piece_steps; ++l) {
         int64_t pieces = 0;
@@ -626,20 +652,107 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   p->n_extend_items = static_cast<int32_t>(nitems);
   p->num_wide = static_cast<int32_t>(wide_order.size());
 
+  // ---- extend blocks cut along their keys ----
+  struct XPart {
+    int32_t xb, st0, st1, part;  // of block xb (before the KV heads); part -1: the whole block
+  };
+  std::vector<XPart> xparts;
+  auto xsteps = [&](const XBlock& xb) {
+    const int32_t a = b->agent[xb.r];
+    const int32_t P = a >= 0 ? pt->prefix_len[a] : 0;
+    const int32_t L = b->suffix_len[xb.r] - p->req[xb.r].n + xb.i1;
+    return (P + kStepKeys - 1) / kStepKeys + (L + kStepKeys - 1) / kStepKeys;
+  };
+  int64_t chunk_slots = 0;
+  if (nitems > 0) {
+    const ChunkCosts& cost = p->d == 128 ? kChunkCosts128 : kChunkCosts64;
+    int32_t cut = 0;
+    if (int64_t(nitems) < kResidentExtend) {
+      int64_t pairs = 0;
+      int32_t longest = 0;
+      for (const XBlock& xb : xbs) {
+        const int32_t n = (xsteps(xb) + 1) / 2;
+        pairs += int64_t(n) * hkv;
+        longest = std::max(longest, n);
+      }
+      // Two workgroups on a compute unit: the longer runs beside the shorter,
+      // then alone.
+      auto time = [&](double longer, double shorter) { return cost.alone * longer + (1 - cost.alone) * shorter; };
+      // Uncut, workgroup i shares with workgroup 256 + i; the blocks are in
+      // launch order, hkv workgroups each.
+      double uncut = 0;
+      for (size_t k = 0; k < xrank.size() && int64_t(k) * hkv < kComputeUnits; ++k) {
+        const size_t other = k + size_t(kComputeUnits / hkv);
+        uncut = std::max(uncut, time((xsteps(xbs[xrank[k]]) + 1) / 2,
+                                     other < xrank.size() ? (xsteps(xbs[xrank[other]]) + 1) / 2 : 0));
+      }
+      double best = 0.9 * uncut;
+      // The shortest pieces that leave every workgroup half a compute unit,
+      // with the decode pieces after them or beside them, or a whole one.
+      for (int64_t room : {kResidentExtend, kResidentExtend - int64_t(npcs), kComputeUnits}) {
+        if (room < kComputeUnits) continue;
+        int64_t c = std::max<int64_t>(kLeastChunkPairs, (pairs + room - 1) / room), count = 0, slots = 0;
+        for (; c < longest; ++c) {
+          count = slots = 0;
+          for (const XBlock& xb : xbs) {
+            const int64_t k = ((xsteps(xb) + 1) / 2 + c - 1) / c;
+            count += k * hkv;
+            slots += k > 1 ? k * hkv : 0;
+          }
+          if (count <= room) break;
+        }
+        if (c >= longest) continue;
+        const double t = time(double(c), count > kComputeUnits ? double(c) : 0) + cost.fixed + cost.slot * double(slots) +
+                         (npcs && count + int64_t(npcs) > kResidentExtend ? cost.late : 0);
+        if (t < best) {
+          best = t;
+          cut = static_cast<int32_t>(c);
+        }
+      }
+    }
+    if (cut) {
+      for (int32_t xi : xrank) {
+        const int32_t steps = xsteps(xbs[xi]), n = (steps + 1) / 2, k = (n + cut - 1) / cut;
+        for (int32_t i = 0; i < k; ++i)
+          xparts.push_back(XPart{xi, int32_t(2 * (int64_t(i) * n / k)), std::min(steps, int32_t(2 * (int64_t(i + 1) * n / k))),
+                                 k > 1 ? i : -1});
+        if (k > 1) chunk_slots += int64_t(k) * hkv;
+      }
+    }
+  }
+  size_t nxmerge = 0;
+
   // ---- workspace layout ----
-  size_t off = 0;
-  p->off_items = off;      off = align256(off + (nitems + wide_order.size()) * sizeof(Item));
-  p->off_row_tok = off;    off = align256(off + p->row_tok.size() * 4);
-  p->off_row_out = off;    off = align256(off + p->row_out.size() * 4);
-  p->off_page_list = off;  off = align256(off + p->page_list.size() * 4);
-  p->off_tok_slot = off;   off = align256(off + p->tok_slot.size() * 4);
-  p->off_segs = off;       off = align256(off + nsegs * sizeof(Seg));
-  p->off_merge_tok = off;  off = align256(off + p->merge_tok.size() * 4);
-  p->off_merge_head = off; off = align256(off + p->merge_head.size() * sizeof(MergeHead));
-  p->blob_bytes = off;
-  p->off_opart = off;      off = align256(off + size_t(p->num_part_rows) * p->d * 2);
-  p->off_lpart = off;      off = align256(off + size_t(p->num_part_rows) * 8);
-  p->total_bytes = std::max<size_t>(off, 256);
+  auto lay_out = [&] {
+    p->num_chunks = static_cast<int32_t>(xparts.size() * size_t(hkv));
+    nxmerge = 0;
+    for (const XPart& x : xparts) nxmerge += x.part == 0 ? size_t(hkv) : 0;
+    size_t off = 0;
+    p->off_items = off;      off = align256(off + (nitems + wide_order.size()) * sizeof(Item));
+    p->off_row_tok = off;    off = align256(off + p->row_tok.size() * 4);
+    p->off_row_out = off;    off = align256(off + p->row_out.size() * 4);
+    p->off_page_list = off;  off = align256(off + p->page_list.size() * 4);
+    p->off_tok_slot = off;   off = align256(off + p->tok_slot.size() * 4);
+    p->off_segs = off;       off = align256(off + nsegs * sizeof(Seg));
+    p->off_merge_tok = off;  off = align256(off + p->merge_tok.size() * 4);
+    p->off_merge_head = off; off = align256(off + p->merge_head.size() * sizeof(MergeHead));
+    p->off_chunks = off;     off = align256(off + size_t(p->num_chunks) * sizeof(Chunk));
+    p->off_chunk_merge = off; off = align256(off + nxmerge * sizeof(ChunkMerge));
+    p->blob_bytes = off;
+    p->off_opart = off;      off = align256(off + size_t(p->num_part_rows) * p->d * 2);
+    p->off_lpart = off;      off = align256(off + size_t(p->num_part_rows) * 8);
+    p->off_xopart = off;     off = align256(off + size_t(chunk_slots) * kExtendTileCols * p->d * 4);
+    p->off_xlpart = off;     off = align256(off + size_t(chunk_slots) * kExtendTileCols * 8);
+    p->total_bytes = std::max<size_t>(off, 256);
+  };
+  lay_out();
+  if (p->num_chunks && p->total_bytes > PFX_NOALLOC_MAX_WORKSPACE) {
+    // Cut blocks may not be what takes a plan past the static workspace.
+    xparts.clear();
+    chunk_slots = 0;
+    lay_out();
+  }
+  p->num_chunk_merges = static_cast<int32_t>(nxmerge);
 
   p->num_items = static_cast<int32_t>(nitems);
   p->num_segs = static_cast<int32_t>(nsegs);
@@ -662,6 +775,8 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
         {p->off_segs, nsegs * sizeof(Seg)},
         {p->off_merge_tok, p->merge_tok.size() * 4},
         {p->off_merge_head, p->merge_head.size() * sizeof(MergeHead)},
+        {p->off_chunks, size_t(p->num_chunks) * sizeof(Chunk)},
+        {p->off_chunk_merge, nxmerge * sizeof(ChunkMerge)},
     };
     const size_t ns = sizeof(sect) / sizeof(sect[0]);
     for (size_t i = 0; i < ns; ++i) {
@@ -683,8 +798,10 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   // ids and first token are filled in here.
   Item* items = reinterpret_cast<Item*>(p->blob.data() + p->off_items);
   size_t nit = 0;
+  std::vector<int32_t> xitem(xbs.size());  // first item of each block
   for (int32_t xi : xrank) {
     const XBlock& xb = xbs[xi];
+    xitem[xi] = static_cast<int32_t>(nit);
     const ReqInfo ri = p->req[xb.r];
     const int32_t a = b->agent[xb.r];
     const int32_t P = a >= 0 ? pt->prefix_len[a] : 0;
@@ -712,6 +829,42 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     for (int32_t h = 0; h < hkv; ++h) {
       it.kv_head = h;
       new (items + nit++) Item(it);
+    }
+  }
+
+  // The pieces of the cut blocks, in launch order: the KV heads of a piece
+  // side by side, as the blocks' own.
+  if (p->num_chunks) {
+    Chunk* chunks = reinterpret_cast<Chunk*>(p->blob.data() + p->off_chunks);
+    ChunkMerge* xm = reinterpret_cast<ChunkMerge*>(p->blob.data() + p->off_chunk_merge);
+    int32_t slot = 0;
+    size_t nc = 0, nm = 0;
+    for (size_t k = 0; k < xparts.size(); ++k) {
+      const XPart& x = xparts[k];
+      const Item& it = items[xitem[x.xb]];
+      const int32_t s0_steps = (it.s0_kend + kStepKeys - 1) / kStepKeys;
+      Chunk c{};
+      c.st0 = x.st0;
+      c.st1 = x.st1;
+      for (int32_t i = 0; i < 2 && x.st0 + i < x.st1; ++i) {
+        const int32_t st = x.st0 + i;
+        const bool pre = st < s0_steps;
+        const int32_t pg = 2 * (pre ? st : st - s0_steps), last = ((pre ? it.s0_kend : it.s1_kend) + 15) / 16 - 1;
+        const int32_t at = pre ? it.s0_page_off : it.s1_page_off;
+        c.pages[2 * i] = p->page_list[at + pg];
+        c.pages[2 * i + 1] = p->page_list[at + std::min(pg + 1, last)];
+      }
+      int32_t parts = 1;
+      if (x.part == 0)
+        while (k + parts < xparts.size() && xparts[k + parts].part > 0) ++parts;
+      for (int32_t h = 0; h < hkv; ++h) {
+        c.item = xitem[x.xb] + h;
+        // Slots: the parts of one (block, KV head) in a row.
+        c.slot = x.part < 0 ? -1 : x.part == 0 ? slot + h * parts : chunks[nc - hkv].slot + 1;
+        if (x.part == 0) new (xm + nm++) ChunkMerge{c.item, c.slot, parts, 0};
+        new (chunks + nc++) Chunk(c);
+      }
+      if (x.part == 0) slot += parts * hkv;
     }
   }
 

@@ -1,0 +1,57 @@
+"""Cut extend blocks on the GPU against the oracle: pieces that start in the
+prefix, in the suffix and on the step between them, rows that see nothing of a
+piece, blocks with padding columns, several blocks and requests, head_dim 64
+and 128, G from 1 to 16, beside decode rows, without LSE, and through the
+allocation-free entry point."""
+
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2608_25523_amd import binding as B  # noqa: E402
+from paper_2608_25523_amd import runner as RN  # noqa: E402
+from paper_2608_25523_amd import workloads as W  # noqa: E402
+from test_gpu_parity import announce, run_and_check  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (Hq, Hkv, d, prefixes, requests (agent, L, n))
+    (32, 8, 128, [1500], [(0, 33, 33)]),
+    (32, 8, 128, [1501], [(0, 300, 70), (0, 20, 1), (-1, 5, 1)]),
+    (32, 8, 128, [], [(-1, 1300, 300)]),
+    (16, 16, 128, [17, 1200], [(0, 40, 40), (1, 130, 130), (-1, 9, 9)]),
+    (32, 2, 64, [2033], [(0, 513, 100), (0, 20, 20), (0, 9, 1)]),
+    (8, 8, 64, [1999], [(0, 129, 129)]),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=[f"chunks{i}" for i in range(len(CASES))])
+def test_cut_blocks(case):
+    hq, hkv, d, plen, reqs = case
+    b = W.make_batch(90, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=512, prefix_len=plen,
+                     agent=[r[0] for r in reqs], suffix_len=[r[1] for r in reqs], n_rows=[r[2] for r in reqs])
+    hv = W.host_values(b, 91)
+    ds, o_ref, l_ref = run_and_check(b, hv, f"chunks Hq={hq} Hkv={hkv} d={d} {plen} {reqs}")
+    # A cut plan's workspace holds the pieces' states: 512 d bytes a piece at least.
+    assert ds.plan.workspace_bytes() > 8 * 512 * d
+    plan = ds.plan
+    run_and_check(b, hv, "chunks, no LSE", with_lse=False)
+    ds = RN.DeviceStep(b, hv)
+    B.pfx_attention_noalloc(ds.pool, plan, ds.q, ds.o, ds.lse, k_new=ds.k_new, v_new=ds.v_new)
+    B.pfx_sync_check()
+    o, l = ds.outputs()
+    assert np.array_equal(o, o_ref) and np.array_equal(l, l_ref)
+    announce("chunks: the allocation-free call gives the same bits")
+
+
+def test_peaked_scores_in_cut_blocks():
+    """Rising and one-hot scores: the pieces' maxima lie far apart."""
+    b = W.make_batch(92, num_q_heads=32, num_kv_heads=8, head_dim=128, num_pages=512, prefix_len=[2000],
+                     agent=[0, 0], suffix_len=[150, 40], n_rows=[150, 40])
+    hv = W.host_values_shaped(b, 93, key_gain=lambda p: 1.0 + p / 256.0, q_gain=4.0, v_gain=0.25)
+    run_and_check(b, hv, "chunks, rising scores")
+    run_and_check(b, W.plant_one_hot(b, W.host_values(b, 94), 95, alpha_log2=4), "chunks, one-hot")

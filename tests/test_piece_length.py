@@ -35,7 +35,7 @@ def test_shortest_length_that_is_resident(d, reqs, plen, extend):
         b = batch(d, reqs, plen, extend)
     s = plan(b).stats()
     assert s.num_decode_steps < 12288
-    room = (512 if d == 128 else 1024) - s.num_extend_items
+    room = 0 if extend else 512 if d == 128 else 1024   # beside extend blocks the pieces stay long
     count = {l: plan(b, piece_steps=l).stats() for l in range(3, 17)}
     fits = [l for l in count if count[l].num_decode_pieces + count[l].num_wide_blocks <= room]
     want = count[min(fits) if fits else 16]
