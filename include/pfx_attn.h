@@ -271,9 +271,9 @@ int pfx_attention(const pfx_pool* pool, const pfx_plan* plan, const void* q, voi
  * extend blocks, the decode launch appends as it goes: a decode request's
  * new tokens are read straight from k_new / v_new into the step that
  * attends them and written into their pool slots by the same workgroup (no
- * other work of the launch reads those slots).  Extend blocks read one
- * another's new tokens, so with extend blocks the append runs first as its
- * own launch.  Arguments as pfx_append_kv and pfx_attention; k_new and
+ * other work of the launch reads those slots).  So do the extend blocks of a
+ * small launch; with many or long ones the append runs first as its own
+ * launch.  Arguments as pfx_append_kv and pfx_attention; k_new and
  * v_new may be NULL only when the plan has no query rows.
  * --------------------------------------------------------------------- */
 int pfx_step(const pfx_pool* pool, const pfx_plan* plan, const void* k_new, const void* v_new, const void* q,

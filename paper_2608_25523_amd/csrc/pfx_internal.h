@@ -54,7 +54,7 @@ struct alignas(16) Item {
   int32_t kind;
   int32_t req;
   int32_t tok0;
-  int32_t pad0;
+  int32_t first_new;  // extend blocks: suffix keys from here on are the step's new tokens (token k - causal_base)
   int32_t first_pages[kItemPages];
 };
 static_assert(sizeof(Item) == 128, "Item is 32 int32");
@@ -141,7 +141,7 @@ struct DevPlan {
   const Seg* segs;              // decode pieces, longest first
   const int32_t* merge_tok;     // decode tokens (their rows are merged from pieces)
   const MergeHead* merge_head;  // [merge token][KV head]
-  const Chunk* chunks;          // pieces of the extend blocks, when some are cut
+  const Chunk* chunks;          // pieces of the extend blocks, when there is a table of them
   const ChunkMerge* chunk_merge;
   uint16_t* o_part;             // [partial row][d] bf16, in the partial layout
   float* l_part;                // [partial row][2]
@@ -166,7 +166,7 @@ struct pfx_plan {
   int32_t num_wide = 0;        // wide prefix blocks, after the extend blocks in the same array
   std::vector<int32_t> row_tok, row_out, page_list, tok_req, tok_slot;
   std::vector<pfx::ReqInfo> req;
-  int32_t num_chunks = 0;      // pieces of the extend blocks (0: none is cut, one workgroup per block)
+  int32_t num_chunks = 0;      // pieces of the extend blocks (0: one workgroup per block, the append before them)
   int32_t num_chunk_merges = 0;  // extend blocks that are cut
   int32_t num_segs = 0;        // decode pieces (their records live in the blob at off_segs)
   int32_t merge_parts = 0;     // P when every merged (row, KV head) has P parts at slots (row * Hkv + h) * P, else 0

@@ -1024,6 +1024,70 @@ __device__ __forceinline__ void issue_block_copy(unsigned char* stage, const Att
   copy_block_to_lds(base, voff, lds_address(stage) + wave * TG::page_bytes);
 }
 
+// The step's new tokens of an extend block, for the folded-in append: suffix
+// keys from it.first_new on are rows of k_new / v_new (token k - causal_base).
+// Issue this wave's tile of step st from there, if it holds any of them.
+// Whole tiles of new tokens are 16 rows hkv * D apart from one base; a tile
+// that also holds old keys, or keys past the block's end (masked, any row
+// will do), takes each lane's row from its own address.  blk: the tile's block
+// in the pool (read only where the tile holds old keys).
+struct NewTile {
+  int32_t key0;  // first key of the tile
+  bool any;
+};
+
+__device__ __forceinline__ NewTile new_tile(const Item& it, const StepMarks& mk, int st, int wave) {
+  int key0 = kStepKeys * (st - mk.s0_steps) + 16 * (wave & 1);
+  if (key0 >= it.s1_kend) key0 -= 16;  // a missing second page re-reads the first
+  return NewTile{key0, st >= mk.s0_steps && key0 + 16 > it.first_new};
+}
+
+template <int D>
+__device__ __forceinline__ void issue_new_tile(unsigned char* stage, const AttnArgs& a, const Item& it, int key0,
+                                               int page, int wave, int lane,
+                                               const uint32_t (&voff)[TileGeom<D>::loads_per_wave]) {
+  using TG = TileGeom<D>;
+  const uint16_t* fresh = (wave >> 1) ? a.v_new : a.k_new;
+  const uint32_t dst = lds_address(stage) + wave * TG::page_bytes;
+  const uint32_t row_bytes = 2u * D * a.hkv;
+  if (key0 >= it.first_new && key0 + 16 <= it.s1_kend) {
+    uint32_t off[TG::loads_per_wave];
+#pragma unroll
+    for (int j = 0; j < TG::loads_per_wave; ++j)
+      off[j] = voff[j] + uint32_t((64 * j + lane) / TG::chunks) * (row_bytes - 2 * D);
+    copy_block_to_lds(fresh + (size_t(key0 - it.causal_base) * a.hkv + it.kv_head) * D, off, dst);
+    return;
+  }
+  PFX_KEEP_BRANCH();
+  const uint16_t* pool = ((wave >> 1) ? a.vpool : a.kpool) + (size_t(page) * a.hkv + it.kv_head) * (16 * D);
+#pragma unroll
+  for (int j = 0; j < TG::loads_per_wave; ++j) {
+    const int t = (64 * j + lane) / TG::chunks;
+    const int c = (lane % TG::chunks) ^ row_key<TG::chunks>(t);
+    const int key = min(key0 + t, it.s1_kend - 1);
+    const uint16_t* src = key >= it.first_new ? fresh + (size_t(key - it.causal_base) * a.hkv + it.kv_head) * D + 8 * c
+                                              : pool + t * D + 8 * c;
+    copy16_to_lds(src, dst + 1024 * j);
+  }
+}
+
+// Write the block's own new tokens' K/V rows into their pool slots (no
+// workgroup of the launch reads those).
+template <int D>
+__device__ __forceinline__ void append_block_rows(const AttnArgs& a, const Item& it) {
+  constexpr int CPR = D / 8;
+  const int per = it.row_count * CPR;
+  for (int e = threadIdx.x; e < 2 * per; e += 256) {
+    const bool is_v = e >= per;
+    const int r = is_v ? e - per : e;
+    const int tok = it.tok0 + r / CPR, c = r % CPR;
+    const int slot = a.plan.tok_slot[tok];
+    const u32x4 x = *reinterpret_cast<const u32x4*>((is_v ? a.v_new : a.k_new) + (size_t(tok) * a.hkv + it.kv_head) * D + 8 * c);
+    uint16_t* pool = const_cast<uint16_t*>(is_v ? a.vpool : a.kpool);
+    *reinterpret_cast<u32x4*>(pool + ((size_t(slot >> 4) * a.hkv + it.kv_head) * 16 + (slot & 15)) * D + 8 * c) = x;
+  }
+}
+
 // Step st's page through the window.  Entries grow by at most 3 from one of
 // this wave's steps to the next, so a step either finds its entry in cur or
 // moves one window on (its successor, requested 64 entries earlier, has
@@ -1046,9 +1110,9 @@ constexpr int extend_smem_bytes() { return kStages * TileGeom<D>::stage_bytes; }
 // for its own copies, all waves meet (the pair's stages complete everywhere,
 // the previous pair's stages consumed), those are refilled two steps ahead,
 // and every wave multiplies the pair against its own columns.
-// C: the workgroup runs only the steps of a piece of the block (*ck) and
-// leaves its state in the piece's slot.
-template <int D, int QBW, bool C = false>
+// C: the workgroup runs only the steps of a piece of the block (*ckp) and
+// leaves its state in the piece's slot.  A (with C): the append is folded in.
+template <int D, int QBW, bool C = false, bool A = false>
 __device__ __forceinline__ void extend_block(const AttnArgs& a, const Item* itp, unsigned char* smem,
                                              const Chunk* ckp = nullptr) {
   using TG = TileGeom<D>;
@@ -1125,35 +1189,62 @@ __device__ __forceinline__ void extend_block(const AttnArgs& a, const Item* itp,
   // The first two steps' pages are among the leading ids (they travel in
   // the block record, one per lane): request them before the page windows
   // arrive.
-  for (int i = 0; i < 2 && first + i < nsteps; ++i)
-    issue_block_copy<D>(ring[i], a,
-                        __builtin_amdgcn_readfirstlane(__builtin_amdgcn_readlane(
-                            lead, C ? 2 * i + (wave & 1) : step_entry(mk, i, wave))),
-                        h, wave, voff);
+  for (int i = 0; i < 2 && first + i < nsteps; ++i) {
+    const int page = __builtin_amdgcn_readfirstlane(
+        __builtin_amdgcn_readlane(lead, C ? 2 * i + (wave & 1) : step_entry(mk, i, wave)));
+    if constexpr (A) {
+      const NewTile nt = new_tile(it, mk, first + i, wave);
+      if (nt.any) {
+        issue_new_tile<D>(ring[i], a, it, nt.key0, page, wave, lane, voff);
+        continue;
+      }
+    }
+    issue_block_copy<D>(ring[i], a, page, h, wave, voff);
+  }
   // Two steps per barrier: at pair q (steps 2q, 2q + 1) wait for both
   // stages, meet (so the stages of the previous pair are free), refill them
   // with steps 2q + 2 and 2q + 3, and run the pair.  Unrolled by two pairs,
   // so every copy of the body works on fixed stages and its LDS addresses
   // are a lane offset plus an immediate.
   static_assert(NS == 4, "pairs of steps in a ring of four stages");
-  for (int st0 = first; st0 < nsteps; st0 += 4) {
+  auto run = [&](int from, int to, auto issue) __attribute__((always_inline)) {
+    for (int st0 = from; st0 < to; st0 += 4) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int st = st0 + 2 * k;
-      if (st >= nsteps) break;
-      const bool two = st + 1 < nsteps;
-      wait_vmcnt(0);
-      __syncthreads();
-      if (st + 2 < nsteps)
-        issue_block_copy<D>(ring[(2 * k + 2) % NS], a, window_page(pw, step_entry(mk, st + 2, wave), lane), h, wave,
-                            voff);
-      if (st + 3 < nsteps)
-        issue_block_copy<D>(ring[(2 * k + 3) % NS], a, window_page(pw, step_entry(mk, st + 3, wave), lane), h, wave,
-                            voff);
-      // An odd last step pairs with an empty one (its stage is not being
-      // refilled).
-      if (nb > 0) extend_pair<D, QBW>(ws, ring[2 * k], ring[2 * k + 1], qf, lim, it, st, two, mk, lane, a.scale_log2);
+      for (int k = 0; k < 2; ++k) {
+        const int st = st0 + 2 * k;
+        if (st >= to) break;
+        const bool two = st + 1 < nsteps;
+        wait_vmcnt(0);
+        __syncthreads();
+        if (st + 2 < nsteps) issue(ring[(2 * k + 2) % NS], st + 2);
+        if (st + 3 < nsteps) issue(ring[(2 * k + 3) % NS], st + 3);
+        // An odd last step pairs with an empty one (its stage is not being
+        // refilled).
+        if (nb > 0)
+          extend_pair<D, QBW>(ws, ring[2 * k], ring[2 * k + 1], qf, lim, it, st, two, mk, lane, a.scale_log2);
+      }
     }
+  };
+  auto from_pool = [&](unsigned char* stage, int st) __attribute__((always_inline)) {
+    issue_block_copy<D>(stage, a, window_page(pw, step_entry(mk, st, wave), lane), h, wave, voff);
+  };
+  if constexpr (A) {
+    // A loop of its own for the steps whose refills may hold new tokens, so
+    // that the loop over the others is the plain one.
+    const int fresh = mk.s0_steps + it.first_new / kStepKeys;  // the first step with new tokens
+    const int mid = min(nsteps, first + (fresh - 2 > first ? (fresh - 2 - first) & ~3 : 0));
+    run(first, mid, from_pool);
+    run(mid, nsteps, [&](unsigned char* stage, int st) __attribute__((always_inline)) {
+      const NewTile nt = new_tile(it, mk, st, wave);
+      const int page = nt.any && nt.key0 >= it.first_new ? 0 : window_page(pw, step_entry(mk, st, wave), lane);
+      if (nt.any) issue_new_tile<D>(stage, a, it, nt.key0, page, wave, lane, voff);
+      else issue_block_copy<D>(stage, a, page, h, wave, voff);
+    });
+  } else {
+    run(first, nsteps, from_pool);
+  }
+  if constexpr (A) {
+    if (first == 0) append_block_rows<D>(a, it);
   }
   if constexpr (C) {
     const int slot = ckp->slot;
@@ -1202,11 +1293,11 @@ __global__ __launch_bounds__(256, 2) void extend_kernel(AttnArgs a) {
 // block in series (300 rows over 4096 keys, Hq 32, Hkv 8, d 128: 80 blocks of
 // 69 pairs on 256 compute units, 92 us a step call with the append; as 480
 // pieces 39 us, of which the pieces take about 24 and their merge 8).
-template <int D>
+template <int D, bool A>
 __global__ __launch_bounds__(256, 2) void extend_chunk_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[extend_smem_bytes<D>()];
   const Chunk* ck = a.plan.chunks + blockIdx.x;
-  extend_block<D, 2, true>(a, a.plan.items + ck->item, smem, ck);
+  extend_block<D, 2, true, A>(a, a.plan.items + ck->item, smem, ck);
 }
 
 // The cut blocks' rows from their pieces' states: one thread per f32x4 of a
@@ -1374,7 +1465,7 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, unsigned cha
   if constexpr (C) {
     if (int(blockIdx.x) < a.num_chunks) {
       const Chunk* ck = a.plan.chunks + blockIdx.x;
-      extend_block<D, 2, true>(a, a.plan.items + ck->item, smem, ck);
+      extend_block<D, 2, true, F>(a, a.plan.items + ck->item, smem, ck);
       return;
     }
   }
@@ -1582,10 +1673,10 @@ __global__ __launch_bounds__(256, 2) void decode_kernel(AttnArgs a) {
 // A mixed batch whose extend blocks are cut.  A kernel of its own: with the
 // pieces' code in decode_kernel, a batch of 32 large prefills and 448 decode
 // requests ran 1.5% slower.
-template <int D>
+template <int D, bool F>
 __global__ __launch_bounds__(256, 2) void mixed_chunk_kernel(AttnArgs a) {
   __shared__ __attribute__((aligned(1024))) unsigned char smem[decode_kernel_smem<D, true, false>()];
-  decode_workgroup<D, false, true, false, true>(a, smem);
+  decode_workgroup<D, F, true, false, true>(a, smem);
 }
 
 // Decode rows: the log-sum-exp merge of the pieces' states (softmax over a
@@ -1870,7 +1961,8 @@ template <int D>
 static void launch_decode(const AttnArgs& a, const pfx_plan* p, hipStream_t s) {
   const dim3 grid(a.num_wide + std::min<int>(a.num_workers, p->num_segs));
   if (a.num_chunks) {
-    hipLaunchKernelGGL((mixed_chunk_kernel<D>), grid, dim3(256), 0, s, a);
+    if (a.fuse_append) hipLaunchKernelGGL((mixed_chunk_kernel<D, true>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((mixed_chunk_kernel<D, false>), grid, dim3(256), 0, s, a);
   } else if (p->decode_engine == PFX_DECODE_VALU) {
     if (a.fuse_append) hipLaunchKernelGGL((decode_kernel<D, true, false, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((decode_kernel<D, false, false, true>), grid, dim3(256), 0, s, a);
@@ -1885,7 +1977,7 @@ static void launch_decode(const AttnArgs& a, const pfx_plan* p, hipStream_t s) {
 
 template <int D>
 static void launch_all(AttnArgs a, const pfx_plan* p, hipStream_t s) {
-  if (p->num_items > 0 && p->num_segs > 0 && p->decode_engine == PFX_DECODE_MFMA && !a.fuse_append) {
+  if (p->num_items > 0 && p->num_segs > 0 && p->decode_engine == PFX_DECODE_MFMA) {
     // A mixed batch in one launch: the extend blocks (or their pieces) and
     // the wide prefix blocks lead the grid (the same block routine as the
     // extend launch, at the same block indices, so their XCD grouping holds),
@@ -1897,7 +1989,10 @@ static void launch_all(AttnArgs a, const pfx_plan* p, hipStream_t s) {
     m.wide_first = p->num_chunks ? p->num_items : 0;
     launch_decode<D>(m, p, s);
   } else {
-    if (p->num_chunks) hipLaunchKernelGGL((extend_chunk_kernel<D>), dim3(p->num_chunks), dim3(256), 0, s, a);
+    if (p->num_chunks && a.fuse_append)
+      hipLaunchKernelGGL((extend_chunk_kernel<D, true>), dim3(p->num_chunks), dim3(256), 0, s, a);
+    else if (p->num_chunks)
+      hipLaunchKernelGGL((extend_chunk_kernel<D, false>), dim3(p->num_chunks), dim3(256), 0, s, a);
     else if (p->num_items > 0) hipLaunchKernelGGL((extend_kernel<D>), dim3(p->num_items), dim3(256), 0, s, a);
     if (p->num_segs > 0 || p->num_wide > 0) launch_decode<D>(a, p, s);
   }
@@ -2015,15 +2110,17 @@ extern "C" int pfx_attention(const pfx_pool* pool, const pfx_plan* p, const void
                           "pfx_attention");
 }
 
-// The append and the attention of one step in the fewest launches: with no
-// extend blocks (which read each other's new tokens) the decode pieces take
-// their new tokens straight from k_new / v_new and write them into the pool
-// themselves; otherwise the append kernel runs first.
+// The append and the attention of one step in the fewest launches: the
+// launches take the step's new tokens straight from k_new / v_new and write
+// them into the pool themselves.  With extend blocks that have no pieces table
+// the append kernel runs first: there it is a small part of the time (48 us of
+// 2750 for 36,864 rows), and the extend loop stays without the test of every
+// tile for new tokens.
 static int step_launches(const pfx_pool* pool, const pfx_plan* p, const DevPlan& dp, const void* k_new,
                          const void* v_new, const void* q, void* o, float* lse, float sm_scale, hipStream_t s,
                          const char* who) {
   const bool attend = p->num_items > 0 || p->num_segs > 0 || p->num_wide > 0;
-  if (p->num_tokens > 0 && (p->num_items > 0 || !attend)) {
+  if (p->num_tokens > 0 && ((p->num_items > 0 && !p->num_chunks) || !attend)) {
     int rc = launch_append(pool, p, dp, k_new, v_new, s, who);
     if (rc || !attend) return rc;
     return launch_attention(pool, p, dp, q, o, lse, sm_scale, s, who);

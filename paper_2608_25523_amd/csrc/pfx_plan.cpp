@@ -83,6 +83,13 @@ constexpr int64_t kResident128 = 512, kResident64 = 1024;
 // 18) 31.5 and 32.7.
 constexpr int64_t kResidentExtend = 512, kComputeUnits = 256;
 constexpr int32_t kLeastChunkPairs = 4;
+// The launch over a pieces table can also take the step's append along
+// (pfx_step), which costs its loop some registers and the tiles of new tokens
+// a longer issue.  Blocks that stay whole go through the table only when none
+// is longer than this: 4 requests of 32 rows over 128 keys 10.6 -> 9.1 us a
+// step call, but 512 rows over 2048 at Hq 64 (40 pairs) 59.0 -> 61.3.  Cut
+// launches gain: 32 rows over 4096 keys 20.7 -> 19.1, 300 39.8 -> 38.4.
+constexpr int32_t kShortPairs = 8;
 struct ChunkCosts {
   double alone, fixed, slot, late;
 };
@@ -666,10 +673,9 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   int64_t chunk_slots = 0;
   if (nitems > 0) {
     const ChunkCosts& cost = p->d == 128 ? kChunkCosts128 : kChunkCosts64;
-    int32_t cut = 0;
+    int32_t cut = 0, longest = 0;
     if (int64_t(nitems) < kResidentExtend) {
       int64_t pairs = 0;
-      int32_t longest = 0;
       for (const XBlock& xb : xbs) {
         const int32_t n = (xsteps(xb) + 1) / 2;
         pairs += int64_t(n) * hkv;
@@ -710,9 +716,9 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
         }
       }
     }
-    if (cut) {
+    if (cut || (int64_t(nitems) < kResidentExtend && longest <= kShortPairs)) {
       for (int32_t xi : xrank) {
-        const int32_t steps = xsteps(xbs[xi]), n = (steps + 1) / 2, k = (n + cut - 1) / cut;
+        const int32_t steps = xsteps(xbs[xi]), n = (steps + 1) / 2, k = cut ? (n + cut - 1) / cut : 1;
         for (int32_t i = 0; i < k; ++i)
           xparts.push_back(XPart{xi, int32_t(2 * (int64_t(i) * n / k)), std::min(steps, int32_t(2 * (int64_t(i + 1) * n / k))),
                                  k > 1 ? i : -1});
@@ -746,7 +752,7 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     p->total_bytes = std::max<size_t>(off, 256);
   };
   lay_out();
-  if (p->num_chunks && p->total_bytes > PFX_NOALLOC_MAX_WORKSPACE) {
+  if (chunk_slots && p->total_bytes > PFX_NOALLOC_MAX_WORKSPACE) {
     // Cut blocks may not be what takes a plan past the static workspace.
     xparts.clear();
     chunk_slots = 0;
@@ -826,6 +832,7 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     for (int32_t pg = it.s1_kbeg >> 4; it.s1_kend > it.s1_kbeg && pg < (it.s1_kend + 15) >> 4 && k < kItemPages; ++pg)
       it.first_pages[k++] = p->page_list[it.s1_page_off + pg];
     it.tok0 = p->row_tok[it.row_begin];
+    it.first_new = L - ri.n;
     for (int32_t h = 0; h < hkv; ++h) {
       it.kv_head = h;
       new (items + nit++) Item(it);

@@ -77,6 +77,6 @@ def test_no_scratch_in_the_piece_kernels(tmp_path):
                    check=True, capture_output=True)
     blocks = [b.split(".end_amdhsa_kernel")[0] for b in out.read_text().split(".amdhsa_kernel ")[1:]]
     mine = [b for b in blocks if any(n in b.split()[0] for n in ("chunk_kernel", "chunk_merge", "merge_parts"))]
-    assert len(mine) == 10
+    assert len(mine) == 14
     for b in mine:
         assert ".amdhsa_private_segment_fixed_size 0" in b, b.split()[0]

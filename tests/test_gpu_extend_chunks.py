@@ -1,8 +1,8 @@
-"""Cut extend blocks on the GPU against the oracle: pieces that start in the
+"""Extend blocks of small launches, cut and whole, on the GPU against the oracle: pieces that start in the
 prefix, in the suffix and on the step between them, rows that see nothing of a
 piece, blocks with padding columns, several blocks and requests, head_dim 64
-and 128, G from 1 to 16, beside decode rows, without LSE, and through the
-allocation-free entry point."""
+and 128, G from 1 to 16, beside decode rows, without LSE, through the
+allocation-free entry point, and with the append folded in."""
 
 from __future__ import annotations
 
@@ -14,7 +14,8 @@ torch = pytest.importorskip("torch")
 from paper_2608_25523_amd import binding as B  # noqa: E402
 from paper_2608_25523_amd import runner as RN  # noqa: E402
 from paper_2608_25523_amd import workloads as W  # noqa: E402
-from test_gpu_parity import announce, run_and_check  # noqa: E402
+from test_gpu_parity import announce, assert_untouched, run_and_check  # noqa: E402
+import parity as PT  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -55,3 +56,38 @@ def test_peaked_scores_in_cut_blocks():
     hv = W.host_values_shaped(b, 93, key_gain=lambda p: 1.0 + p / 256.0, q_gain=4.0, v_gain=0.25)
     run_and_check(b, hv, "chunks, rising scores")
     run_and_check(b, W.plant_one_hot(b, W.host_values(b, 94), 95, alpha_log2=4), "chunks, one-hot")
+
+
+# (Hq, Hkv, d, prefixes, requests): new tokens that start inside a page, on a
+# page and on a step, end on each of those, and share a page with old ones.
+# Every row sees 17 keys or more: over two or three N(0, 1) values |O| passes 2,
+# where the rounding of O alone is half of 2^-6 and with P's (2^-9 of each
+# term) goes past the stated 1e-2.
+STEPS = [
+    (32, 8, 128, [1500], [(0, 300, 70), (0, 48, 32), (0, 64, 32), (0, 50, 33), (-1, 40, 23), (0, 20, 1), (0, 9, 4)]),
+    (8, 2, 64, [100], [(0, 32, 32), (0, 47, 16), (-1, 34, 17), (0, 33, 5), (0, 16, 1)]),
+    (16, 16, 128, [40], [(0, 140, 130), (0, 31, 31), (0, 90, 17), (-1, 48, 32)]),
+    (32, 2, 64, [1000], [(0, 700, 51), (0, 65, 64), (-1, 37, 3)]),
+]
+
+
+@pytest.mark.parametrize("engine", [B.PFX_DECODE_MFMA, B.PFX_DECODE_VALU])
+@pytest.mark.parametrize("case", STEPS, ids=[f"step{i}" for i in range(len(STEPS))])
+def test_step_with_extend_blocks(case, engine):
+    """pfx_step with the append folded into the extend blocks: outputs and pool
+    equal append + attention bit for bit, other pages untouched."""
+    hq, hkv, d, plen, reqs = case
+    b = W.make_batch(96, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=512, prefix_len=plen,
+                     agent=[r[0] for r in reqs], suffix_len=[r[1] for r in reqs], n_rows=[r[2] for r in reqs])
+    hv = W.host_values(b, 97)
+    ds, o_ref, l_ref = run_and_check(b, hv, f"step over {plen} {reqs}", decode_engine=engine)
+    del ds
+    ds = RN.DeviceStep(b, hv, decode_engine=engine)
+    B.pfx_step(ds.pool, ds.plan, ds.k_new, ds.v_new, ds.q, ds.o, ds.lse)
+    B.pfx_sync_check()
+    o, l = ds.outputs()
+    assert np.array_equal(o, o_ref) and np.array_equal(l, l_ref)
+    exp_k, exp_v = PT.expected_pools(b, hv)
+    gk, gv = ds.read_pages(hv.pages)
+    assert np.array_equal(gk, exp_k) and np.array_equal(gv, exp_v)
+    assert_untouched(ds, hv.pages, "step with extend blocks")
