@@ -167,6 +167,9 @@ struct AttnArgs {
   // extend blocks (mixed_chunk_kernel), then the blocks items[wide_first ...] (extend or wide
   // prefix blocks), the others the decode pieces.
   int32_t num_wide, wide_first, num_chunks;
+  // Decode launch: blocks that are dealt out in turn with the pieces (see
+  // launch_decode).
+  int32_t dealt;
   // Merge launch: P when every (merge row m, KV head h) has P parts from
   // slot (m Hkv + h) P (then merge_head is not read), else 0; and 1 when
   // merge row m is token m for every m (then the merge with the append
@@ -1449,6 +1452,9 @@ __device__ __forceinline__ int issue_piece_stage(unsigned char* stage, const Att
   return TG::loads_per_wave;
 }
 
+// Blocks, then pieces, in runs of this many workgroups where they take turns.
+constexpr int kDealRun = 128;
+
 // F: the append is folded in.  W: the launch starts with wide prefix blocks.
 // V: the pieces run on the vector ALU (no wide blocks then).
 // C: before those, pieces of extend blocks.
@@ -1469,11 +1475,22 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, unsigned cha
       return;
     }
   }
+  int bid = blockIdx.x;  // position among the blocks, then the pieces
+  if constexpr (W && !C) {
+    // The first `dealt` blocks and as many pieces take turns in the grid.
+    const int dealt = a.dealt;
+    if (bid < 2 * dealt) {
+      const int i = bid / (2 * kDealRun) * kDealRun + bid % kDealRun;
+      bid = bid / kDealRun % 2 ? a.num_wide + i : i;
+    } else if (bid < dealt + a.num_wide) {
+      bid -= dealt;
+    }
+  }
   if constexpr (W) {
-    if (int(blockIdx.x) < a.num_wide) {
+    if (bid < a.num_wide) {
       // A wide prefix block: 128 decode columns against one piece of their
       // agent's prefix, the extend block's two-steps-per-barrier pipeline.
-      extend_block<D, 2>(a, a.plan.items + a.wide_first + (blockIdx.x - (C ? a.num_chunks : 0)), smem);
+      extend_block<D, 2>(a, a.plan.items + a.wide_first + (bid - (C ? a.num_chunks : 0)), smem);
       return;
     }
   }
@@ -1482,7 +1499,7 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, unsigned cha
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int col = lane & 15, grp = lane >> 4;
-  const int S = int(gridDim.x) - a.num_wide, b = int(blockIdx.x) - a.num_wide;
+  const int S = int(gridDim.x) - a.num_wide, b = bid - a.num_wide;
   const int np = a.num_pieces;
 
   // The first two descriptors.
@@ -1957,9 +1974,24 @@ static int check_pool_matches(const pfx_pool* pool, const pfx_plan* p, const cha
 
 // The decode launch: extend or wide prefix blocks (a.num_wide of them from
 // a.wide_first) and the pieces.
+//
+// Wide blocks are matrix work on a prefix that stays in the L2, pieces stream
+// their keys from HBM.  In a decode-only launch at d = 128 they take turns in
+// the grid, in runs of 128 workgroups (16 on each XCD, so that a run lands on
+// half of the compute units and the next on the others), for as long as both
+// last: a unit then holds one of each instead of the two kinds following one
+// another.  448 requests of 8 agents, 8192-token prefixes, Hq 64 (1024 blocks,
+// 3584 pieces) 482 -> 440 us; 320 of 6 (640, 2560) 260 -> 239; 400 of 4 at Hq
+// 32 (256, 3200) 127.3 -> 121.4; fewer blocks than a run stay in front.  Runs
+// of 8 put two blocks on every other unit (400 requests: 144 us), runs of 512
+// change nothing; at d = 64, four workgroups a unit, runs of 128 lose 2%.  In
+// front of a mixed batch the extend blocks stay together (spread among the
+// pieces they ran 5% slower).
 template <int D>
-static void launch_decode(const AttnArgs& a, const pfx_plan* p, hipStream_t s) {
-  const dim3 grid(a.num_wide + std::min<int>(a.num_workers, p->num_segs));
+static void launch_decode(AttnArgs a, const pfx_plan* p, hipStream_t s) {
+  const int pieces = std::min<int>(a.num_workers, p->num_segs);
+  if (D == 128 && p->num_items == 0) a.dealt = std::min(a.num_wide, pieces) / kDealRun * kDealRun;
+  const dim3 grid(a.num_wide + pieces);
   if (a.num_chunks) {
     if (a.fuse_append) hipLaunchKernelGGL((mixed_chunk_kernel<D, true>), grid, dim3(256), 0, s, a);
     else hipLaunchKernelGGL((mixed_chunk_kernel<D, false>), grid, dim3(256), 0, s, a);
@@ -2085,6 +2117,7 @@ static int launch_attention(const pfx_pool* pool, const pfx_plan* p, const DevPl
   a.num_wide = p->num_wide;
   a.wide_first = p->num_items;
   a.num_chunks = 0;
+  a.dealt = 0;
   a.merge_parts = p->merge_parts;
   a.merge_tok_is_row = p->merge_tok_is_row;
   if (p->d == 128) launch_all<128>(a, p, s); else launch_all<64>(a, p, s);
