@@ -1939,9 +1939,22 @@ __global__ __launch_bounds__(256) void append_kernel(const uint16_t* k_new, cons
   *reinterpret_cast<u32x4*>(d + dst) = *reinterpret_cast<const u32x4*>(s + src);
 }
 
-// grid (chunks of a page, pages, 2 for K/V); pairs[2i] = dst page, pairs[2i+1] = src page.
+// The page lists of a copy: pairs[2i] = dst page, pairs[2i+1] = src page, in
+// device memory, or in the kernel's arguments.
+struct PairsAt {
+  const int32_t* at;
+  __device__ __forceinline__ int32_t operator[](size_t i) const { return at[i]; }
+};
+constexpr int kArgPairs = 448;  // 3.5 KiB of arguments
+struct PairsHere {
+  int32_t pair[2 * kArgPairs];
+  __device__ __forceinline__ int32_t operator[](size_t i) const { return pair[i]; }
+};
+
+// grid (chunks of a page, pages, 2 for K/V).
+template <typename Pairs>
 __global__ __launch_bounds__(256) void page_copy_kernel(const u32x4* src_k, const u32x4* src_v, u32x4* dst_k,
-                                                        u32x4* dst_v, const int32_t* pairs, size_t page_vecs) {
+                                                        u32x4* dst_v, Pairs pairs, size_t page_vecs) {
   const size_t v = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
   if (v >= page_vecs) return;
   const int i = blockIdx.y;
@@ -1950,6 +1963,29 @@ __global__ __launch_bounds__(256) void page_copy_kernel(const u32x4* src_k, cons
     dst_k[dp * page_vecs + v] = src_k[sp * page_vecs + v];
   else
     dst_v[dp * page_vecs + v] = src_v[sp * page_vecs + v];
+}
+
+// Reads from host memory are bound by the link (57 GB/s by the copy engines),
+// which 64 workgroups of one load a thread keep busy.  More requests at once
+// only queue on the way: 128 pages (8.4 MB) took 192 us with a workgroup for
+// every 4 KiB, here about 152, and the decode attention beside a 134 MB load 71
+// us a call, here 57 (29 alone).  Writes to host memory gain nothing from it
+// (154 us either way) and are gentler on attention with all workgroups at once
+// (54 us a call against 96).
+constexpr int kLinkWorkgroups = 64;
+
+template <typename Pairs>
+__global__ __launch_bounds__(256) void page_load_kernel(const u32x4* src_k, const u32x4* src_v, u32x4* dst_k,
+                                                        u32x4* dst_v, Pairs pairs, size_t page_vecs, int n) {
+  const size_t per_page = (page_vecs + 255) / 256, per_side = per_page * n;
+  for (size_t c = blockIdx.x; c < 2 * per_side; c += gridDim.x) {
+    const bool is_v = c >= per_side;
+    const size_t r = is_v ? c - per_side : c;
+    const size_t i = r / per_page, v = (r - i * per_page) * 256 + threadIdx.x;
+    if (v >= page_vecs) continue;
+    const size_t dp = size_t(pairs[2 * i]), sp = size_t(pairs[2 * i + 1]);
+    (is_v ? dst_v : dst_k)[dp * page_vecs + v] = (is_v ? src_v : src_k)[sp * page_vecs + v];
+  }
 }
 
 static int hip_fail(hipError_t e, const char* what) {
@@ -2299,27 +2335,41 @@ extern "C" int pfx_page_copy(const pfx_pool* dst, const pfx_pool* src, const int
   }
   // Every page array must be device memory or pinned host memory (the
   // kernel would fault on pageable host memory).
+  bool from_host = false;
   for (const void* ptr : {dst->k_pages, dst->v_pages, src->k_pages, src->v_pages}) {
     hipPointerAttribute_t at;
     if (hipPointerGetAttributes(&at, ptr) != hipSuccess) {
       (void)hipGetLastError();
       return fail(PFX_EINVAL, "pfx_page_copy: a page pointer is neither device nor pinned host memory");
     }
+    from_host |= at.type == hipMemoryTypeHost && (ptr == src->k_pages || ptr == src->v_pages);
   }
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipError_t e = hipMemcpyAsync(ws, pairs.data(), pairs.size() * 4, hipMemcpyHostToDevice, s);
-  if (e != hipSuccess) return hip_fail(e, "pfx_page_copy: hipMemcpyAsync");
   const size_t page_bytes = size_t(dst->num_kv_heads) * PFX_PAGE_SIZE * dst->head_dim * 2;
   const size_t page_vecs = page_bytes / 16;
+  auto launch = [&](const auto& list, int32_t cnt) {
+    typedef std::decay_t<decltype(list)> Pairs;
+    const auto sk = static_cast<const u32x4*>(src->k_pages), sv = static_cast<const u32x4*>(src->v_pages);
+    const auto dk = static_cast<u32x4*>(dst->k_pages), dv = static_cast<u32x4*>(dst->v_pages);
+    if (from_host)
+      hipLaunchKernelGGL((page_load_kernel<Pairs>), dim3(kLinkWorkgroups), dim3(256), 0, s, sk, sv, dk, dv, list,
+                         page_vecs, cnt);
+    else
+      hipLaunchKernelGGL((page_copy_kernel<Pairs>), dim3((page_vecs + 255) / 256, cnt, 2), dim3(256), 0, s, sk, sv,
+                         dk, dv, list, page_vecs);
+    return check_launch("pfx_page_copy");
+  };
+  if (n <= kArgPairs) {
+    // A short list travels in the launch itself: no copy in front of it.
+    PairsHere list;
+    std::copy(pairs.begin(), pairs.end(), list.pair);
+    return launch(list, n);
+  }
+  hipError_t e = hipMemcpyAsync(ws, pairs.data(), pairs.size() * 4, hipMemcpyHostToDevice, s);
+  if (e != hipSuccess) return hip_fail(e, "pfx_page_copy: hipMemcpyAsync");
   // gridDim.y is limited to 65535: launch the page list in slices.
   for (int32_t at = 0; at < n; at += 65535) {
-    const int32_t cnt = std::min<int32_t>(65535, n - at);
-    const dim3 grid((page_vecs + 255) / 256, cnt, 2);
-    hipLaunchKernelGGL(page_copy_kernel, grid, dim3(256), 0, s, static_cast<const u32x4*>(src->k_pages),
-                       static_cast<const u32x4*>(src->v_pages), static_cast<u32x4*>(dst->k_pages),
-                       static_cast<u32x4*>(dst->v_pages), static_cast<const int32_t*>(ws) + 2 * size_t(at),
-                       page_vecs);
-    int rc = check_launch("pfx_page_copy");
+    const int rc = launch(PairsAt{static_cast<const int32_t*>(ws) + 2 * size_t(at)}, std::min<int32_t>(65535, n - at));
     if (rc) return rc;
   }
   return PFX_OK;
