@@ -34,6 +34,7 @@ CASES = [
     (32, 8, 128, [17, 3000], [(0, 40, 40), (1, 40, 40), (-1, 9, 9)], True),   # long and short blocks together
     (16, 16, 128, [2049], [(0, 201, 201), (0, 30, 1)], True),
     (32, 2, 64, [2048], [(0, 513, 100), (0, 20, 20)], True),
+    (32, 8, 128, [8000], [(0, 1200, 1200)], True),           # two rounds of pieces
     (32, 8, 128, [1000], [(0, 100, 100)] * 8, False),        # short blocks: a second launch costs more
     (32, 8, 128, [2048], [(0, 1999, 1999)], False),          # the chip is full already
     (8, 2, 64, [128], [(0, 32, 32)] * 4, False),
@@ -64,7 +65,7 @@ def test_pieces_cover_every_block(tmp_path):
     for line, case in zip(lines, CASES):
         assert (not line.startswith("cut 0 ")) == case[-1], (case, line)
         if case[-1]:
-            assert int(line.split(", ")[1].split()[0]) <= 512
+            assert int(line.split(", ")[1].split()[0]) <= 1024
 
 
 @pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="hipcc not available")
