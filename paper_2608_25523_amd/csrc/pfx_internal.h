@@ -173,6 +173,7 @@ struct pfx_plan {
   int32_t max_parts = 0;         // most parts of a merged (row, KV head)
   int32_t merge_tok_is_row = 0;  // 1 when merge row m is decode token m for every m
   int64_t num_decode_steps = 0;
+  bool deal_wide = false;      // the decode pieces hold at least as many steps as the wide blocks
   std::vector<int32_t> merge_tok;
   std::vector<pfx::MergeHead> merge_head;
   int64_t num_part_rows = 0;

@@ -2018,7 +2018,9 @@ static int check_pool_matches(const pfx_pool* pool, const pfx_plan* p, const cha
 // last: a unit then holds one of each instead of the two kinds following one
 // another.  448 requests of 8 agents, 8192-token prefixes, Hq 64 (1024 blocks,
 // 3584 pieces) 482 -> 440 us; 320 of 6 (640, 2560) 260 -> 239; 400 of 4 at Hq
-// 32 (256, 3200) 127.3 -> 121.4; fewer blocks than a run stay in front.  Runs
+// 32 (256, 3200) 127.3 -> 121.4; fewer blocks than a run stay in front, and so
+// do blocks with more steps than the pieces (56 requests of 25 to 50 tokens of
+// their own over 8192: the blocks wait behind short pieces, 32.6 -> 34.9).  Runs
 // of 8 put two blocks on every other unit (400 requests: 144 us), runs of 512
 // change nothing; at d = 64, four workgroups a unit, runs of 128 lose 2%.  In
 // front of a mixed batch the extend blocks stay together (spread among the
@@ -2026,7 +2028,7 @@ static int check_pool_matches(const pfx_pool* pool, const pfx_plan* p, const cha
 template <int D>
 static void launch_decode(AttnArgs a, const pfx_plan* p, hipStream_t s) {
   const int pieces = std::min<int>(a.num_workers, p->num_segs);
-  if (D == 128 && p->num_items == 0) a.dealt = std::min(a.num_wide, pieces) / kDealRun * kDealRun;
+  if (D == 128 && p->num_items == 0 && p->deal_wide) a.dealt = std::min(a.num_wide, pieces) / kDealRun * kDealRun;
   const dim3 grid(a.num_wide + pieces);
   if (a.num_chunks) {
     if (a.fuse_append) hipLaunchKernelGGL((mixed_chunk_kernel<D, true>), grid, dim3(256), 0, s, a);

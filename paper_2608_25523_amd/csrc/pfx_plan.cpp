@@ -596,6 +596,9 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   std::vector<int32_t> wide_order, seg_order;
   for (int32_t k : order) (is_wide(k) ? wide_order : seg_order).push_back(k);
   const size_t nsegs = seg_order.size();
+  int64_t wide_steps = 0;
+  for (int32_t k : wide_order) wide_steps += pcs[k].s1 - pcs[k].s0;
+  p->deal_wide = p->num_decode_steps - wide_steps >= wide_steps;
   if (nsegs > size_t(INT32_MAX) || wide_order.size() > size_t(INT32_MAX))
     return delete p, fail(PFX_ERANGE, "pfx_plan_create: too many decode pieces");
 
@@ -659,7 +662,8 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   // block has the shortest beside it.  504 blocks, 1999 rows over 2048 keys:
   // 110.8 -> 107.6 us a step call at d = 128, 74.5 -> 73.2 at d = 64; 2000 rows
   // over 16 keys 56.4 -> 54.0; where the lengths hardly differ nothing changes.
-  if (int64_t(nitems) > kComputeUnits && int64_t(nitems) <= kResidentExtend && kComputeUnits % hkv == 0)
+  // (Beside decode pieces the launch is fuller than that.)
+  if (int64_t(nitems) > kComputeUnits && int64_t(nitems) <= kResidentExtend && npcs == 0 && kComputeUnits % hkv == 0)
     std::reverse(xrank.begin() + kComputeUnits / hkv, xrank.end());
   if (nitems + wide_order.size() > size_t(INT32_MAX))
     return delete p, fail(PFX_ERANGE, "pfx_plan_create: too many extend blocks");

@@ -18,7 +18,7 @@ CASES = [
     (40, 256, dict(piece_steps=1), 128),                        # one run of blocks
     (40, 300, dict(piece_steps=1), 160),                        # one run and a part
     (40, 220, dict(piece_steps=1), 112),                        # less than a run
-    (20, 1024, dict(piece_steps=1), 256),                       # fewer pieces than blocks
+    (20, 1024, dict(piece_steps=1), 256),                       # more steps in the blocks: they stay in front
     (40, 300, dict(piece_steps=1, decode_workers=140), 160),
 ]
 
