@@ -43,9 +43,10 @@ static int64_t pages_for(int64_t tokens) { return (tokens + PFX_PAGE_SIZE - 1) /
 // turn over 16 pools (nothing of K/V left in the last-level cache), Hq 32,
 // Hkv 8, d 128, us per step call.
 //   From kLongPiecesFrom steps on: 64.
-//   From kMidPiecesFrom on: 32.  100 requests of 4 agents (13464 steps) 51.9
+//   From kMidPiecesFrom on at d = 128: 32.  100 requests of 4 agents (13464 steps) 51.9
 //   at 16, 49.4 at 32, 65.0 at 64; 160 of 8 (25408) 90.2, 85.8, 86.2; 64
-//   requests of 4 agents (7032) 30.0 at 16, 38.9 at 32.
+//   requests of 4 agents (7032) 30.0 at 16, 38.9 at 32.  At d = 64 it gains
+//   nothing (24286 steps: 49.5 at 16, 49.8 at 32).
 //   Below: the shortest from kLeastPieceSteps on with which the whole launch
 //   is resident at once, else 16.  A launch that size is bound by its longest
 //   workgroup, about 0.75 us a step after 4.5 us of start, not by memory, and
@@ -440,9 +441,9 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   if (piece_steps == 0) {
     int64_t steps = 0;
     for (const DItem& x : dit) steps += item_steps(x);
-    piece_steps = steps >= kLongPiecesFrom  ? kLongPieceSteps
-                  : steps >= kMidPiecesFrom ? kMidPieceSteps
-                                            : kDefaultPieceSteps;
+    piece_steps = steps >= kLongPiecesFrom                   ? kLongPieceSteps
+                  : steps >= kMidPiecesFrom && p->d == 128 ? kMidPieceSteps
+                                                           : kDefaultPieceSteps;
     int64_t room = p->d == 128 ? kResident128 : kResident64;
     // Beside extend blocks, which take longer, the pieces stay long.
     for (int32_t r = 0; r < R && room > 0; ++r)
