@@ -170,11 +170,12 @@ typedef struct pfx_plan_opts {
    * timing. */
   int32_t decode_workers;
   /* Longest decode piece, in 32-key steps (0 = automatic: 64 when the decode
-   * items hold at least 32768 steps, 32 from 12288 at
-   * head_dim 128, otherwise at most 16 and
-   * as short as keeps all workgroups resident at once, 3 at least; at most
-   * 64).  Shorter pieces balance the workgroups better but give each decode
-   * row more partial results to merge. */
+   * items hold at least 32768 steps, 32 from 12288 at head_dim 128, otherwise
+   * at most 16 and as short as keeps all workgroups resident at once, 3 at
+   * least; at most 64).  Shorter pieces balance the workgroups better but
+   * give each decode row more partial results to merge.  The automatic length
+   * follows the batch, so a row may differ by rounding between batches that
+   * get different lengths; a fixed length avoids that. */
   int32_t piece_steps;
   /* Engine of the decode pieces: PFX_DECODE_MFMA (0, the default: matrix
    * cores, and wide prefix blocks for agents with more than 64 decode
