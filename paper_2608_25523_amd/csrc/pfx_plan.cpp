@@ -56,6 +56,13 @@ static int64_t pages_for(int64_t tokens) { return (tokens + PFX_PAGE_SIZE - 1) /
 //   280); 16 of three agents 20.4 -> 16.9 (7, 456); 32 of four 21.7 -> 20.1
 //   (11, 496).  Two steps a piece: 11.8 and 12.8 for the first two.  More
 //   workgroups than fit: 19.5 (6, 528) and 21.3 (6, 744) for the last two.
+//   A request without a prefix whose keys fit one piece of 16 steps keeps
+//   them in one: its sums stay fp32 until the one rounding of its state, which
+//   the merge of a lone part repeats exactly.  In 3-step pieces a row of 288
+//   N(0, 1) keys would be 2.7e-3 off instead of 2.2e-3 (2-norm).  A shorter
+//   length for the other rows of such a launch would not shorten it: it ends
+//   with its longest piece.  (Rows with a prefix have two states or more at
+//   any length and are 2.7e-3 off with any number of them.)
 constexpr int32_t kDefaultPieceSteps = 16;
 constexpr int32_t kMidPieceSteps = 32;
 constexpr int64_t kMidPiecesFrom = 12288;
@@ -448,8 +455,15 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     // Beside extend blocks, which take longer, the pieces stay long.
     for (int32_t r = 0; r < R && room > 0; ++r)
       if (p->req[r].n > 0 && !is_decode_class(r)) room = 0;
+    int32_t least = kLeastPieceSteps;
+    for (int32_t r = 0; r < R; ++r) {
+      const size_t rh = size_t(r) * hkv;
+      if (sf_item[rh] < 0 || pf_item[rh] >= 0) continue;
+      const int32_t lone = item_steps(dit[sf_item[rh]]);
+      if (lone <= kDefaultPieceSteps) least = std::max(least, lone);
+    }
     if (room > 0 && int64_t(dit.size()) <= room)
-      for (int64_t l = std::max<int64_t>(kLeastPieceSteps, (steps + room - 1) / room); l < piece_steps; ++l) {
+      for (int64_t l = std::max<int64_t>(least, (steps + room - 1) / room); l < piece_steps; ++l) {
         int64_t pieces = 0;
         for (const DItem& x : dit) pieces += (item_steps(x) + l - 1) / l;
         if (pieces <= room) piece_steps = static_cast<int32_t>(l);

@@ -43,3 +43,16 @@ def test_merge_part_counts(parts, d, hq, hkv):
     assert np.array_equal(gk, exp_k) and np.array_equal(gv, exp_v)
     assert_untouched(ds, hv.pages, "merge-parts step")
     announce(f"merge parts {parts} d={d}: step equals append + attention")
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(128, 32, 8), (64, 8, 2)])
+def test_lone_short_items_round_once(d, hq, hkv):
+    """Requests without a prefix, of 97 to 512 keys, in a small launch: the
+    bits of 16-step pieces, which hold each row in one fp32 state."""
+    lens = [97, 160, 288, 512]
+    b = W.make_batch(310, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=512, prefix_len=[700],
+                     agent=[-1] * 4 + [0], suffix_len=lens + [100], n_rows=[1] * 5)
+    hv = W.host_values(b, 311)
+    _, o16, l16 = run_and_check(b, hv, f"lone items, 16 steps, d={d}", piece_steps=16)
+    _, o, l = run_and_check(b, hv, f"lone items, d={d}")
+    assert np.array_equal(o[:4], o16[:4]) and np.array_equal(l[:4], l16[:4])

@@ -47,3 +47,19 @@ def test_length_of_larger_launches():
     s = plan(b).stats()
     assert 12288 <= s.num_decode_steps < 32768
     assert s.num_decode_pieces == plan(b, piece_steps=32).stats().num_decode_pieces
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(128, 32, 8), (64, 8, 2), (128, 16, 16)])
+@pytest.mark.parametrize("keys,parts", [(97, 1), (160, 1), (288, 1), (512, 1), (513, 0)])
+def test_lone_short_items_stay_whole(d, hq, hkv, keys, parts):
+    """A request whose only item fits one piece of 16 steps has one state, as
+    with 16-step pieces, whatever else is in the launch; a longer one is cut."""
+    def parts_of(reqs, plen, **kw):
+        b = W.make_batch(8, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=1024, prefix_len=plen,
+                         agent=[r[0] for r in reqs], suffix_len=[r[1] for r in reqs], n_rows=[1] * len(reqs))
+        return plan(b, **kw).export(7)[:, 1].reshape(len(reqs), hkv)
+    for reqs, plen in (([(-1, keys)], []), ([(-1, 20), (-1, keys), (-1, 40)], []), ([(0, keys)], [0]),
+                       ([(0, 200), (-1, keys), (0, 300)], [2048])):
+        got = parts_of(reqs, plen)
+        lone = [i for i, r in enumerate(reqs) if r[1] == keys]
+        assert np.array_equal(got[lone], parts_of(reqs, plen, piece_steps=16)[lone]) if parts else (got[lone] > 1).all()
