@@ -106,8 +106,9 @@ struct alignas(16) SegHead {
   int32_t causal;       // 1: some row sees only part of the keys (multi-row suffix)
   int32_t pad[5];
 };
-// One piece as stored in the workspace and, unchanged, in a workgroup's LDS
-// slot.
+// One piece in a workgroup's LDS slot, room for the most rows and steps.  Its
+// record in the workspace holds the same sections, each as long as the plan's
+// largest piece needs (SegShape).
 struct alignas(16) Seg {
   SegHead h;
   int32_t tok[kSegRows];          // query token of row j
@@ -116,6 +117,20 @@ struct alignas(16) Seg {
   int32_t steps[2 * kPieceSteps]; // per step: (page * Hkv + head) of its two 16-key pages
 };
 static_assert(sizeof(Seg) == 1088, "Seg is 272 int32");
+
+// Lengths of the records' sections in 16-byte vectors: the header, tok, out
+// (row_vecs each) and steps (step_vecs).  A record is what planning writes, an
+// upload copies and a workgroup waits for first, so it does not carry room
+// that no piece of the plan uses.  Four requests over 2048 + 200 to 600 keys,
+// 344 pieces of 3 steps, 128 bytes each instead of 1088: planned in 30 us
+// instead of 44 through the binding, and a step with its plan and upload takes
+// 64 us instead of 89 (80 pieces of 16 steps in records of 1088 bytes: 24 and
+// 66).  256 requests of 16 agents, pieces of 64 steps: 477 instead of 500.
+struct SegShape {
+  int32_t row_vecs = 1, step_vecs = 1;
+  static constexpr int32_t kHeadVecs = int32_t(sizeof(SegHead)) / 16;
+  constexpr int32_t vecs() const { return kHeadVecs + 2 * row_vecs + step_vecs; }
+};
 
 // Partial results of one (decode token, KV head): nparts slots of G rows at
 // o_part/l_part rows (base + slot) * G + g.  A partial row holds a piece's
@@ -138,7 +153,8 @@ struct DevPlan {
   const int32_t* row_out;       // partial row base of each row of a wide prefix block
   const int32_t* page_list;
   const int32_t* tok_slot;      // page * 16 + slot of every new token (append)
-  const Seg* segs;              // decode pieces, longest first
+  const uint32_t* segs;         // records of the decode pieces, longest first
+  SegShape seg_shape;
   const int32_t* merge_tok;     // decode tokens (their rows are merged from pieces)
   const MergeHead* merge_head;  // [merge token][KV head]
   const Chunk* chunks;          // pieces of the extend blocks, when there is a table of them
@@ -169,6 +185,7 @@ struct pfx_plan {
   int32_t num_chunks = 0;      // pieces of the extend blocks (0: one workgroup per block, the append before them)
   int32_t num_chunk_merges = 0;  // extend blocks that are cut
   int32_t num_segs = 0;        // decode pieces (their records live in the blob at off_segs)
+  pfx::SegShape seg_shape;
   int32_t merge_parts = 0;     // P when every merged (row, KV head) has P parts at slots (row * Hkv + h) * P, else 0
   int32_t max_parts = 0;         // most parts of a merged (row, KV head)
   int32_t merge_tok_is_row = 0;  // 1 when merge row m is decode token m for every m

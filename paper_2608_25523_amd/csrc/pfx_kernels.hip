@@ -1384,6 +1384,16 @@ constexpr int decode_smem_bytes() {
 // Piece of workgroup b at position n of its list (>= num_pieces: none).
 __device__ __forceinline__ int piece_of(int b, int n, int S) { return n * S + ((n & 1) ? S - 1 - b : b); }
 
+// 16-byte vector of a piece's record that vector i of its LDS slot comes from.
+// A record's sections are as long as the plan's largest piece needs; the rest
+// of a slot's sections, which no piece reads, repeats their last vector.
+__device__ __forceinline__ int seg_vec(int i, const SegShape& s) {
+  constexpr int H = SegShape::kHeadVecs, R = kSegRows / 4;
+  asm("" : "+v"(i));  // computed where it is used: kept for the whole launch it takes registers from the loop
+  return min(i, H + s.row_vecs - 1) + min(max(i - (H + R - 1), 0), s.row_vecs) +
+         min(max(i - (H + 2 * R - 1), 0), s.step_vecs);
+}
+
 // Block ids of this wave's tile (wave & 1) for the steps of a piece, one per
 // lane: a step finds its page with v_readlane.
 __device__ __forceinline__ int piece_window(const Seg& sg, int wave, int lane) {
@@ -1507,7 +1517,8 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, unsigned cha
     const int piece = piece_of(b, i / kVecs, S);
     if (piece < np)
       reinterpret_cast<u32x4*>(&slots[i / kVecs])[i % kVecs] =
-          reinterpret_cast<const u32x4*>(&a.plan.segs[piece])[i % kVecs];
+          reinterpret_cast<const u32x4*>(a.plan.segs)[size_t(piece) * a.plan.seg_shape.vecs() +
+                                                      seg_vec(i % kVecs, a.plan.seg_shape)];
   }
   __syncthreads();
 
@@ -1558,10 +1569,10 @@ __device__ __forceinline__ void decode_workgroup(const AttnArgs& a, unsigned cha
         const int nxt = piece_of(b, iord + 2, S);
         if (nxt < np) {
           // Two copies: 16-byte chunks lane and 64 + lane (lanes 0 .. kVecs - 65).
-          const unsigned char* src = reinterpret_cast<const unsigned char*>(&a.plan.segs[nxt]);
+          const u32x4* src = reinterpret_cast<const u32x4*>(a.plan.segs) + size_t(nxt) * a.plan.seg_shape.vecs();
           const uint32_t dst = lds_address(reinterpret_cast<const unsigned char*>(&slots[(iord + 2) % K]));
-          copy16_to_lds(src + 16 * lane, dst);
-          if (lane < kVecs - 64) copy16_to_lds(src + 16 * (64 + lane), dst + 1024);
+          copy16_to_lds(src + seg_vec(lane, a.plan.seg_shape), dst);
+          if (lane < kVecs - 64) copy16_to_lds(src + seg_vec(64 + lane, a.plan.seg_shape), dst + 1024);
           n_ops += 2;
         }
       }

@@ -111,7 +111,8 @@ DevPlan dev_plan(const pfx_plan* p, void* ws) {
   d.row_out = reinterpret_cast<const int32_t*>(base + p->off_row_out);
   d.page_list = reinterpret_cast<const int32_t*>(base + p->off_page_list);
   d.tok_slot = reinterpret_cast<const int32_t*>(base + p->off_tok_slot);
-  d.segs = reinterpret_cast<const Seg*>(base + p->off_segs);
+  d.segs = reinterpret_cast<const uint32_t*>(base + p->off_segs);
+  d.seg_shape = p->seg_shape;
   d.merge_tok = reinterpret_cast<const int32_t*>(base + p->off_merge_tok);
   d.merge_head = reinterpret_cast<const MergeHead*>(base + p->off_merge_head);
   d.o_part = reinterpret_cast<uint16_t*>(base + p->off_opart);
@@ -121,6 +122,21 @@ DevPlan dev_plan(const pfx_plan* p, void* ws) {
   d.xo_part = reinterpret_cast<float*>(base + p->off_xopart);
   d.xl_part = reinterpret_cast<float*>(base + p->off_xlpart);
   return d;
+}
+
+// The piece records of a plan at their full length.
+static std::vector<Seg> full_segs(const pfx_plan* p) {
+  std::vector<Seg> segs(size_t(p->num_segs), Seg{});
+  const size_t rows = size_t(p->seg_shape.row_vecs) * 16, steps = size_t(p->seg_shape.step_vecs) * 16;
+  const unsigned char* at = p->blob.data() + p->off_segs;
+  for (Seg& sg : segs) {
+    std::memcpy(&sg.h, at, sizeof(SegHead));
+    std::memcpy(sg.tok, at + sizeof(SegHead), rows);
+    std::memcpy(sg.out, at + sizeof(SegHead) + rows, rows);
+    std::memcpy(sg.steps, at + sizeof(SegHead) + 2 * rows, steps);
+    at += size_t(p->seg_shape.vecs()) * 16;
+  }
+  return segs;
 }
 
 }  // namespace pfx
@@ -384,6 +400,7 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     int64_t step_first;
     int32_t npieces;
     int32_t wide;             // a prefix item of up to 128 columns, run as wide blocks (32 columns per wave)
+    bool shared;              // a prefix item whose keys another block of the agent's rows reads too
   };
   std::vector<DItem> dit;
   std::vector<int32_t> drow_tok;
@@ -402,6 +419,7 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     // (wide blocks): half the stages, each with twice the products.
     const int32_t wide = engine == PFX_DECODE_MFMA && agent_cols > kDecodeTileCols;
     const int32_t block_cols = wide ? kExtendTileCols : kDecodeTileCols;
+    const size_t first_item = dit.size();
     size_t i = 0;
     while (i < members.size()) {
       // A block of rows whose columns (rows x G) fit one item.
@@ -417,10 +435,11 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
       const int32_t rows = static_cast<int32_t>(drow_tok.size()) - first;
       for (int32_t h = 0; h < hkv; ++h) {
         for (int32_t r : in_block) pf_item[size_t(r) * hkv + h] = static_cast<int32_t>(dit.size());
-        dit.push_back(DItem{kPrefixItem, h, pt->prefix_len[a], prefix_off[a], 0, first, rows, 0, 0, wide});
+        dit.push_back(DItem{kPrefixItem, h, pt->prefix_len[a], prefix_off[a], 0, first, rows, 0, 0, wide, false});
         ++p->n_prefix_items;
       }
     }
+    for (size_t k = first_item; k < dit.size(); ++k) dit[k].shared = dit.size() - first_item > size_t(hkv);
   }
   for (int32_t r = 0; r < R; ++r) {
     if (!is_decode_class(r)) continue;
@@ -430,7 +449,7 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     for (int32_t t = 0; t < ri.n; ++t) drow_tok.push_back(ri.q_start + t);
     for (int32_t h = 0; h < hkv; ++h) {
       sf_item[size_t(r) * hkv + h] = static_cast<int32_t>(dit.size());
-      dit.push_back(DItem{kSuffixItem, h, L, suffix_off[r], L - ri.n - ri.q_start, first, ri.n, 0, 0, 0});
+      dit.push_back(DItem{kSuffixItem, h, L, suffix_off[r], L - ri.n - ri.q_start, first, ri.n, 0, 0, 0, false});
       ++p->n_suffix_items;
     }
   }
@@ -570,7 +589,9 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
       const bool prefix = is_prefix(rank[i]);
       size_t j = i;
       while (j < npcs && pcost[rank[j]] == cost && is_prefix(rank[j]) == prefix) ++j;
-      if (!prefix) {
+      bool shared = false;
+      for (size_t k = i; k < j; ++k) shared |= dit[pcs[rank[k]].item].shared;
+      if (!shared) {  // every chunk has one block
         order.insert(order.end(), rank.begin() + i, rank.begin() + j);
         i = j;
         continue;
@@ -616,6 +637,12 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   p->deal_wide = p->num_decode_steps - wide_steps >= wide_steps;
   if (nsegs > size_t(INT32_MAX) || wide_order.size() > size_t(INT32_MAX))
     return delete p, fail(PFX_ERANGE, "pfx_plan_create: too many decode pieces");
+  for (int32_t k : seg_order) {
+    const Piece& pc = pcs[k];
+    p->seg_shape.row_vecs = std::max(p->seg_shape.row_vecs, (dit[pc.item].rows + 3) / 4);
+    p->seg_shape.step_vecs = std::max(p->seg_shape.step_vecs, (2 * (pc.s1 - pc.s0) + 3) / 4);
+  }
+  const size_t seg_bytes = size_t(p->seg_shape.vecs()) * 16;
 
   // ---- extend blocks (Sec. 3): up to 128 query columns of one request,
   // over the whole prefix (no mask) then the suffix (causal), written
@@ -768,7 +795,7 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     p->off_row_out = off;    off = align256(off + p->row_out.size() * 4);
     p->off_page_list = off;  off = align256(off + p->page_list.size() * 4);
     p->off_tok_slot = off;   off = align256(off + p->tok_slot.size() * 4);
-    p->off_segs = off;       off = align256(off + nsegs * sizeof(Seg));
+    p->off_segs = off;       off = align256(off + nsegs * seg_bytes);
     p->off_merge_tok = off;  off = align256(off + p->merge_tok.size() * 4);
     p->off_merge_head = off; off = align256(off + p->merge_head.size() * sizeof(MergeHead));
     p->off_chunks = off;     off = align256(off + size_t(p->num_chunks) * sizeof(Chunk));
@@ -807,7 +834,7 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
         {p->off_row_out, p->row_out.size() * 4},
         {p->off_page_list, p->page_list.size() * 4},
         {p->off_tok_slot, p->tok_slot.size() * 4},
-        {p->off_segs, nsegs * sizeof(Seg)},
+        {p->off_segs, nsegs * seg_bytes},
         {p->off_merge_tok, p->merge_tok.size() * 4},
         {p->off_merge_head, p->merge_head.size() * sizeof(MergeHead)},
         {p->off_chunks, size_t(p->num_chunks) * sizeof(Chunk)},
@@ -928,36 +955,40 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   }
 
   // The piece records, in launch order.
-  Seg* segs = reinterpret_cast<Seg*>(p->blob.data() + p->off_segs);
+  unsigned char* segs = p->blob.data() + p->off_segs;
+  std::memset(segs, 0, nsegs * seg_bytes);
   for (size_t k = 0; k < nsegs; ++k) {
     const Piece& pc = pcs[seg_order[k]];
     const DItem& x = dit[pc.item];
     const int32_t npages = static_cast<int32_t>(pages_for(x.keys));
-    Seg& sg = *new (segs + k) Seg{};
-    sg.h.kind = x.kind;
-    sg.h.kv_head = x.h;
-    sg.h.ncols = x.rows * G;
-    sg.h.nsteps = pc.s1 - pc.s0;
-    sg.h.k0 = pc.s0 * kStepKeys;
-    sg.h.kend = x.keys;
-    sg.h.causal_base = x.causal_base;
-    sg.h.causal = x.kind == kSuffixItem && x.rows > 1;
-    sg.h.item = pc.item;
-    sg.h.piece = pc.piece;
+    SegHead& h = *new (segs + k * seg_bytes) SegHead{};
+    int32_t* tok = reinterpret_cast<int32_t*>(&h + 1);
+    int32_t* out_row = tok + 4 * p->seg_shape.row_vecs;
+    int32_t* steps = out_row + 4 * p->seg_shape.row_vecs;
+    h.kind = x.kind;
+    h.kv_head = x.h;
+    h.ncols = x.rows * G;
+    h.nsteps = pc.s1 - pc.s0;
+    h.k0 = pc.s0 * kStepKeys;
+    h.kend = x.keys;
+    h.causal_base = x.causal_base;
+    h.causal = x.kind == kSuffixItem && x.rows > 1;
+    h.item = pc.item;
+    h.piece = pc.piece;
     for (int32_t i = pc.s0; i < pc.s1; ++i) {
       const int32_t pg0 = 2 * i, pg1 = 2 * i + 1 < npages ? 2 * i + 1 : 2 * i;  // a missing page repeats (masked)
-      sg.steps[2 * (i - pc.s0)] = page_blk(x, pg0);
-      sg.steps[2 * (i - pc.s0) + 1] = page_blk(x, pg1);
+      steps[2 * (i - pc.s0)] = page_blk(x, pg0);
+      steps[2 * (i - pc.s0) + 1] = page_blk(x, pg1);
     }
     for (int32_t j = 0; j < x.rows; ++j) {
-      const int32_t tok = drow_tok[x.row_first + j];
-      const int32_t r = p->tok_req[tok];
+      const int32_t t = drow_tok[x.row_first + j];
+      const int32_t r = p->tok_req[t];
       const size_t rh = size_t(r) * hkv + x.h;
-      sg.tok[j] = tok;
+      tok[j] = t;
       const int32_t slot = (x.kind == kPrefixItem ? 0 : np_prefix[rh]) + pc.piece;
-      sg.h.slot = slot;  // the same for every row of the piece
-      const size_t mrow = size_t(req_mrow[r]) + (tok - p->req[r].q_start);
-      sg.out[j] = (p->merge_head[mrow * hkv + x.h].base + slot) * G;
+      h.slot = slot;  // the same for every row of the piece
+      const size_t mrow = size_t(req_mrow[r]) + (t - p->req[r].q_start);
+      out_row[j] = (p->merge_head[mrow * hkv + x.h].base + slot) * G;
     }
   }
 
@@ -993,12 +1024,17 @@ extern "C" int pfx_plan_export(const pfx_plan* p, int32_t which, int32_t* out, i
   if (!p || !count) return fail(PFX_EINVAL, "pfx_plan_export: NULL argument");
   const int32_t* src = nullptr;
   int64_t n = 0;
+  std::vector<pfx::Seg> segs;  // the records in full
   switch (which) {
     case 0: src = reinterpret_cast<const int32_t*>(p->host_items()); n = int64_t(p->num_items + p->num_wide) * 32; break;
     case 1: src = p->row_tok.data(); n = int64_t(p->row_tok.size()); break;
     case 8: src = p->row_out.data(); n = int64_t(p->row_out.size()); break;
     case 2: src = p->page_list.data(); n = int64_t(p->page_list.size()); break;
-    case 3: src = reinterpret_cast<const int32_t*>(p->host_segs()); n = int64_t(p->num_segs) * 272; break;
+    case 3:
+      n = int64_t(p->num_segs) * 272;
+      if (cap > 0 && out) segs = pfx::full_segs(p);
+      src = reinterpret_cast<const int32_t*>(segs.data());
+      break;
     case 6: src = p->merge_tok.data(); n = int64_t(p->merge_tok.size()); break;
     case 7: src = reinterpret_cast<const int32_t*>(p->merge_head.data()); n = int64_t(p->merge_head.size()) * 2; break;
     default: return fail(PFX_EINVAL, "pfx_plan_export: which = %d", which);

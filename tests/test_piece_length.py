@@ -63,3 +63,14 @@ def test_lone_short_items_stay_whole(d, hq, hkv, keys, parts):
         got = parts_of(reqs, plen)
         lone = [i for i, r in enumerate(reqs) if r[1] == keys]
         assert np.array_equal(got[lone], parts_of(reqs, plen, piece_steps=16)[lone]) if parts else (got[lone] > 1).all()
+
+
+@pytest.mark.parametrize("reqs,plen,most", [(1, [2048], 32), (4, [2048], 64), (16, [700, 3000, 1500], 128)])
+def test_short_pieces_have_short_records(reqs, plen, most):
+    """What a plan writes and an upload copies does not grow with the pieces of
+    a small launch: no more than 16-step pieces in records of 1088 bytes."""
+    b = batch(128, reqs, plen)
+    s, long = plan(b).stats(), plan(b, piece_steps=16).stats()
+    assert s.num_decode_pieces > long.num_decode_pieces
+    tables = s.workspace_bytes - 264 * s.num_partial_rows
+    assert tables < most << 10 and tables < 1088 * long.num_decode_pieces
