@@ -1867,13 +1867,14 @@ __global__ __launch_bounds__(128) void merge_rows_kernel(AttnArgs a, int n_tok) 
   if constexpr (F) merge_append_store(ap);
 }
 
-// Rows of more parts: the four waves of a workgroup take every fourth part of
-// the same 64 units, kMergeBatch at a time, and meet in LDS.  A merge of few
-// rows is bound by its chain of loads: one thread taking a unit's parts in
-// turn past the first eight pays a round trip for each (one request, 2048 +
-// 288 keys, 8 heads: a step at 2-step pieces, 37 parts a row, 27.4 us, here
-// 11.8 us).  Up to eight parts one thread has them all in flight, and four
-// waves would only add the meeting.
+// Launches with rows of more parts: the four waves of a workgroup take every
+// fourth part of the same 64 units, kMergeBatch at a time, and meet in LDS.  A
+// merge of few rows is bound by its chain of loads: one thread taking a unit's
+// parts in turn past the first eight pays a round trip for each (one request,
+// 2048 + 288 keys, 8 heads: a step at 2-step pieces, 37 parts a row, 27.4 us,
+// here 11.8 us).  Rows of up to eight parts are one thread's here too, in
+// merge_rows_kernel's order: how a row's parts are summed follows from their
+// number, not from the other rows of the launch.
 template <int D, bool F>
 __global__ __launch_bounds__(256) void merge_parts_kernel(AttnArgs a, int n_tok) {
   __shared__ float meet[3][10][64];
@@ -1887,7 +1888,9 @@ __global__ __launch_bounds__(256) void merge_parts_kernel(AttnArgs a, int n_tok)
   }
   const MergeSource src = merge_source<D>(a, sp);
   const int tok = a.plan.merge_tok[sp.m];
-  MergeState s = merge_batch<D>(src, wave, 4);
+  const bool few = src.nparts <= kMergeBatch;
+  const int step = few ? 1 : 4;
+  MergeState s = merge_batch<D>(src, few && wave ? src.nparts : wave, step);
   for (int k = wave + 4 * kMergeBatch; k < src.nparts; k += 4 * kMergeBatch) merge_add(s, merge_batch<D>(src, k, 4));
   if (wave) {
     float(*w)[64] = meet[wave - 1];
@@ -1911,7 +1914,7 @@ __global__ __launch_bounds__(256) void merge_parts_kernel(AttnArgs a, int n_tok)
       o.acc0[e] = meet[x][2 + e][lane];
       o.acc1[e] = meet[x][6 + e][lane];
     }
-    merge_add(s, o);
+    if (!few) merge_add(s, o);
   }
   merge_write<D>(a, sp, tok, s);
   if constexpr (F) merge_append_store(ap);

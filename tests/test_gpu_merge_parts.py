@@ -56,3 +56,22 @@ def test_lone_short_items_round_once(d, hq, hkv):
     _, o16, l16 = run_and_check(b, hv, f"lone items, 16 steps, d={d}", piece_steps=16)
     _, o, l = run_and_check(b, hv, f"lone items, d={d}")
     assert np.array_equal(o[:4], o16[:4]) and np.array_equal(l[:4], l16[:4])
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(128, 32, 8), (64, 6, 3)])
+def test_rows_do_not_depend_on_longer_ones(d, hq, hkv):
+    """At a fixed piece length a request without a prefix has the same bits
+    alone and beside one whose rows have more than eight parts."""
+    for parts in (1, 4, 8, 9):
+        lens = [32 * 4 * parts - 5, 32 * 4 * 10]
+        b = W.make_batch(420, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=512, prefix_len=[],
+                         agent=[-1, -1], suffix_len=lens, n_rows=[1, 1])
+        hv = W.host_values(b, 420)
+        ds, o2, l2 = run_and_check(b, hv, f"{parts} parts beside 10, d={d}", piece_steps=4)
+        assert ds.plan.export(7)[:, 1].reshape(2, hkv)[:, 0].tolist() == [parts, 10]
+        alone = B.pfx_plan_create(ds.pool, [0], [], [], [-1], [0, len(b.suffix_pages[0])], b.suffix_pages[0],
+                                  lens[:1], [0, 1], hq, B.PFX_MODE_DECODE, piece_steps=4).upload()
+        B.pfx_attention(ds.pool, alone, ds.q, ds.o, ds.lse)
+        B.pfx_sync_check()
+        o1, l1 = ds.outputs()
+        assert np.array_equal(o1[0], o2[0]) and np.array_equal(l1[0], l2[0])
