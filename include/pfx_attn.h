@@ -169,13 +169,19 @@ typedef struct pfx_plan_opts {
    * are pieces).  The work division does not depend on it, only its
    * timing. */
   int32_t decode_workers;
-  /* Longest decode piece, in 32-key steps (0 = automatic: 64 when the decode
-   * items hold at least 32768 steps, 32 from 12288 at head_dim 128, otherwise
-   * at most 16 and as short as keeps all workgroups resident at once, 3 at
-   * least; at most 64).  Shorter pieces balance the workgroups better but
-   * give each decode row more partial results to merge.  The automatic length
-   * follows the batch, so a row may differ by rounding between batches that
-   * get different lengths; a fixed length avoids that. */
+  /* Longest decode piece, in 32-key steps, at most 64 (0 = automatic: 64 when
+   * the decode items hold at least 32768 steps, 32 from 12288 at head_dim 128,
+   * 16 below, or as short as keeps all workgroups resident at once where that
+   * is shorter, 3 at least; never shorter than the only item of a request
+   * without a prefix, up to 16).  Shorter pieces balance the workgroups better
+   * but give each decode row more partial results to merge.
+   * The automatic division follows the batch: a decode row's pieces, and
+   * whether the extend blocks of a small launch are cut along their keys, may
+   * change with the other requests, and rows then differ by rounding between
+   * batches.  With a fixed length extend blocks stay whole, and the results of
+   * an extend row, and of a decode row without a prefix, follow from their own
+   * request alone.  (Decode rows that share a prefix are computed together, so
+   * those may still differ by rounding with the other rows of their agent.) */
   int32_t piece_steps;
   /* Engine of the decode pieces: PFX_DECODE_MFMA (0, the default: matrix
    * cores, and wide prefix blocks for agents with more than 64 decode

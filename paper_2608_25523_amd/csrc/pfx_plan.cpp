@@ -83,7 +83,9 @@ constexpr int64_t kResident128 = 512, kResident64 = 1024;
 //   cut: the longest piece (likewise), `fixed` for the second launch, `slot`
 //     for every piece's state, `late` when decode pieces of the batch (16
 //     steps, 16 us) have to wait for them.
-// The blocks are cut when that saves a tenth.  Measured, us a step call uncut
+// The blocks are cut when that saves a tenth, and never at a fixed piece
+// length: how a row is summed then does not follow from the rest of the batch,
+// and the workspace holds no states of theirs.  Measured, us a step call uncut
 // and cut, Hq 32, Hkv 8, d 128: 300 rows over 4096 keys (80 blocks of 69
 // pairs) 92 and 39; 32 rows over 4096 (8 of 65) 86 and 21; 700 over 8192 (176
 // of 139) 178 and 128; 1000 over 4096 (256 of 80) 107 and 90; left uncut: 1999
@@ -266,8 +268,9 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
                   opts->decode_engine);
     p_workers = opts->decode_workers;
     engine = opts->decode_engine;
-    if (opts->piece_steps) piece_steps = opts->piece_steps;
+    piece_steps = opts->piece_steps;
   }
+  const bool fixed_division = piece_steps != 0;  // the work is not cut by what else is in the batch
   if (int64_t(pool->num_pages) * hkv > INT32_MAX)
     return fail(PFX_EUNSUPPORTED, "pfx_plan_create: num_pages * num_kv_heads must stay below 2^31");
 
@@ -751,7 +754,7 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
       // (304 blocks: 1200 rows over 8192 keys 236 -> 191 us a step call, two
       // requests of 600 over 6000 177 -> 148).
       for (int64_t room : {kResidentExtend, kResidentExtend - int64_t(npcs), kComputeUnits, 2 * kResidentExtend}) {
-        if (room < kComputeUnits) continue;
+        if (room < kComputeUnits || fixed_division) continue;
         int64_t c = std::max<int64_t>(kLeastChunkPairs, (pairs + room - 1) / room), count = 0, slots = 0;
         for (; c < longest; c += 1 + c / 32) {  // finer steps would change a piece by less than 3%
           count = slots = 0;

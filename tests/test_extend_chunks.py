@@ -12,6 +12,7 @@ import pytest
 
 pytest.importorskip("torch")
 
+from paper_2608_25523_amd import binding as B  # noqa: E402
 from paper_2608_25523_amd import workloads as W  # noqa: E402
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -66,6 +67,20 @@ def test_pieces_cover_every_block(tmp_path):
         assert (not line.startswith("cut 0 ")) == case[-1], (case, line)
         if case[-1]:
             assert int(line.split(", ")[1].split()[0]) <= 1024
+
+
+@pytest.mark.parametrize("case", [c for c in CASES if c[-1]], ids=lambda c: f"{c[0]}-{c[3]}-{c[4][0][2]}")
+def test_fixed_length_keeps_blocks_whole(case):
+    """With a piece length given, a plan holds no states of cut blocks."""
+    hq, hkv, d, plen, reqs, _ = case
+    b = W.make_batch(32, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=2048, prefix_len=plen,
+                     agent=[r[0] for r in reqs], suffix_len=[r[1] for r in reqs], n_rows=[r[2] for r in reqs])
+    pool = B.make_pool(b.num_pages, hkv, d)
+    states = 8 * 128 * 4 * d  # of one block in two, at the least
+    assert B.plan_from_batch(pool, b).workspace_bytes() > states
+    for steps in (16, 64):
+        s = B.plan_from_batch(pool, b, piece_steps=steps).stats()
+        assert s.workspace_bytes - s.num_partial_rows * (2 * d + 8) < 64 << 10
 
 
 @pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="hipcc not available")

@@ -91,3 +91,25 @@ def test_step_with_extend_blocks(case, engine):
     gk, gv = ds.read_pages(hv.pages)
     assert np.array_equal(gk, exp_k) and np.array_equal(gv, exp_v)
     assert_untouched(ds, hv.pages, "step with extend blocks")
+
+
+@pytest.mark.parametrize("d", [64, 128])
+def test_fixed_length_rows_do_not_depend_on_the_batch(d):
+    """At a fixed piece length an extend request, short or long, has the same
+    bits alone, among other prefills and beside decode rows."""
+    lens, rows = [300, 40, 260, 700, 50], [90, 40, 33, 700, 1]
+    def batch(k):
+        return W.make_batch(99, num_q_heads=32, num_kv_heads=8, head_dim=d, num_pages=512, prefix_len=[200],
+                            agent=[0] * 5, suffix_len=lens, n_rows=[n if i in k else 0 for i, n in enumerate(rows)])
+    hv = W.host_values(batch(range(5)), 100)
+    row0 = np.concatenate([[0], np.cumsum(rows)])
+    ds, o, l = run_and_check(batch(range(5)), hv, f"fixed length, all, d={d}", piece_steps=16)
+    for k in ([0], [1], [2], [3], [1, 4]):
+        plan = B.plan_from_batch(ds.pool, batch(k), piece_steps=16).upload()
+        q = torch.cat([ds.q[row0[i]:row0[i + 1]] for i in k])
+        ok, lk = torch.empty_like(q), torch.empty(q.shape[:2], dtype=torch.float32, device="cuda")
+        B.pfx_attention(ds.pool, plan, q, ok, lk)
+        B.pfx_sync_check()
+        n = rows[k[0]]
+        assert np.array_equal(RN.to_host_bits(ok[:n]), o[row0[k[0]]:row0[k[0] + 1]])
+        assert np.array_equal(lk[:n].cpu().numpy(), l[row0[k[0]]:row0[k[0] + 1]])
