@@ -97,9 +97,9 @@ def test_step_with_extend_blocks(case, engine):
 def test_fixed_length_rows_do_not_depend_on_the_batch(d):
     """At a fixed piece length an extend request, short or long, has the same
     bits alone, among other prefills and beside decode rows."""
-    lens, rows = [300, 40, 260, 700, 50], [90, 40, 33, 700, 1]
+    lens, rows = [300, 40, 260, 700, 50], [90, 40, 33, 300, 1]
     def batch(k):
-        return W.make_batch(99, num_q_heads=32, num_kv_heads=8, head_dim=d, num_pages=512, prefix_len=[200],
+        return W.make_batch(99, num_q_heads=32, num_kv_heads=8, head_dim=d, num_pages=512, prefix_len=[1500],
                             agent=[0] * 5, suffix_len=lens, n_rows=[n if i in k else 0 for i, n in enumerate(rows)])
     hv = W.host_values(batch(range(5)), 100)
     row0 = np.concatenate([[0], np.cumsum(rows)])
