@@ -216,7 +216,11 @@ typedef struct pfx_plan_stats {
 int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* prefixes, const pfx_batch* batch,
                     int32_t num_q_heads, int32_t mode, const pfx_plan_opts* opts, pfx_plan** out);
 
-/* Bytes of device workspace the plan needs (work lists, partial states). */
+/* Bytes of device workspace the plan needs (work lists, partial states).  The
+ * states are most of it, and they do not grow with the batch alone: a batch
+ * with few extend blocks may have them cut along their keys, with 66 KB (128
+ * columns in fp32, head_dim 128) for each piece, up to 69 MB, while a larger
+ * one keeps its blocks whole. */
 int pfx_plan_workspace_bytes(const pfx_plan* plan, size_t* bytes);
 
 /* Counts describing the plan (host only). */
@@ -232,10 +236,13 @@ int pfx_plan_get_stats(const pfx_plan* plan, pfx_plan_stats* out);
  * Writes min(cap, size) values and sets *count to the full size. */
 int pfx_plan_export(const pfx_plan* plan, int32_t which, int32_t* out, int64_t cap, int64_t* count);
 
-/* Copy the plan into a caller-owned device workspace of at least
- * pfx_plan_workspace_bytes bytes (PFX_ENOMEM if smaller) and clear its
- * counters, asynchronously on the stream.  The plan remembers the workspace;
- * pfx_append_kv and pfx_attention use it until the next upload.  The
+/* Copy the plan into a caller-owned device workspace of
+ * pfx_plan_workspace_bytes bytes or more, asynchronously on the stream.  The
+ * plan remembers the workspace; pfx_append_kv, pfx_attention and pfx_step use
+ * it until the next upload.  A smaller workspace that only lacks room for the
+ * pieces of cut extend blocks is taken too: the blocks then stay whole, as at
+ * a fixed piece length (a workspace sized for a program's largest batch serves
+ * its small prefills).  Any smaller one is refused (PFX_ENOMEM).  The
  * workspace (256-byte aligned) must not be shared by calls that may overlap. */
 int pfx_plan_upload(pfx_plan* plan, void* dev_workspace, size_t bytes, void* hip_stream);
 

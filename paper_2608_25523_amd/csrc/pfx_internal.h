@@ -157,7 +157,9 @@ struct DevPlan {
   SegShape seg_shape;
   const int32_t* merge_tok;     // decode tokens (their rows are merged from pieces)
   const MergeHead* merge_head;  // [merge token][KV head]
-  const Chunk* chunks;          // pieces of the extend blocks, when there is a table of them
+  int32_t num_chunks;           // pieces of the extend blocks (0: one workgroup per block)
+  int32_t num_chunk_merges;     // extend blocks that are cut
+  const Chunk* chunks;
   const ChunkMerge* chunk_merge;
   uint16_t* o_part;             // [partial row][d] bf16, in the partial layout
   float* l_part;                // [partial row][2]
@@ -200,6 +202,7 @@ struct pfx_plan {
   size_t off_items = 0, off_row_tok = 0, off_row_out = 0, off_page_list = 0, off_tok_slot = 0, off_segs = 0,
          off_merge_tok = 0, off_merge_head = 0, off_opart = 0, off_lpart = 0, off_chunks = 0, off_chunk_merge = 0, off_xopart = 0, off_xlpart = 0,
          total_bytes = 0, blob_bytes = 0;
+  size_t whole_bytes = 0;  // the least workspace: without the pieces of cut blocks and their states
   std::vector<unsigned char> blob;  // host image of [0, blob_bytes)
   const pfx::Item* host_items() const { return reinterpret_cast<const pfx::Item*>(blob.data() + off_items); }
   const pfx::Seg* host_segs() const { return reinterpret_cast<const pfx::Seg*>(blob.data() + off_segs); }
@@ -213,6 +216,7 @@ int fail(int code, const char* fmt, ...);
 void clear_error();
 // Device pointers of the plan's tables and partial states in a copy of its
 // workspace image at `base` (the uploaded workspace by default).
-pfx::DevPlan dev_plan(const pfx_plan* p, void* base);
-inline pfx::DevPlan dev_plan(const pfx_plan* p) { return dev_plan(p, p->dev_ws); }
+// The plan in a workspace of `bytes` bytes.
+pfx::DevPlan dev_plan(const pfx_plan* p, void* base, size_t bytes);
+inline pfx::DevPlan dev_plan(const pfx_plan* p) { return dev_plan(p, p->dev_ws, p->dev_ws_bytes); }
 }  // namespace pfx

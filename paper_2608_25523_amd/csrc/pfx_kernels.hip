@@ -2061,6 +2061,7 @@ static void launch_decode(AttnArgs a, const pfx_plan* p, hipStream_t s) {
 
 template <int D>
 static void launch_all(AttnArgs a, const pfx_plan* p, hipStream_t s) {
+  const int chunks = a.plan.num_chunks;
   if (p->num_items > 0 && p->num_segs > 0 && p->decode_engine == PFX_DECODE_MFMA) {
     // A mixed batch in one launch: the extend blocks (or their pieces) and
     // the wide prefix blocks lead the grid (the same block routine as the
@@ -2068,20 +2069,20 @@ static void launch_all(AttnArgs a, const pfx_plan* p, hipStream_t s) {
     // and the decode pieces follow, taking compute units as the extend blocks
     // retire instead of waiting for the last of them.
     AttnArgs m = a;
-    m.num_chunks = p->num_chunks;
-    m.num_wide = (p->num_chunks ? p->num_chunks : p->num_items) + p->num_wide;
-    m.wide_first = p->num_chunks ? p->num_items : 0;
+    m.num_chunks = chunks;
+    m.num_wide = (chunks ? chunks : p->num_items) + p->num_wide;
+    m.wide_first = chunks ? p->num_items : 0;
     launch_decode<D>(m, p, s);
   } else {
-    if (p->num_chunks && a.fuse_append)
-      hipLaunchKernelGGL((extend_chunk_kernel<D, true>), dim3(p->num_chunks), dim3(256), 0, s, a);
-    else if (p->num_chunks)
-      hipLaunchKernelGGL((extend_chunk_kernel<D, false>), dim3(p->num_chunks), dim3(256), 0, s, a);
+    if (chunks && a.fuse_append)
+      hipLaunchKernelGGL((extend_chunk_kernel<D, true>), dim3(chunks), dim3(256), 0, s, a);
+    else if (chunks)
+      hipLaunchKernelGGL((extend_chunk_kernel<D, false>), dim3(chunks), dim3(256), 0, s, a);
     else if (p->num_items > 0) hipLaunchKernelGGL((extend_kernel<D>), dim3(p->num_items), dim3(256), 0, s, a);
     if (p->num_segs > 0 || p->num_wide > 0) launch_decode<D>(a, p, s);
   }
-  if (p->num_chunk_merges) {
-    const dim3 grid(p->num_chunk_merges * (kExtendTileCols * D / 4 / 256));
+  if (a.plan.num_chunk_merges) {
+    const dim3 grid(a.plan.num_chunk_merges * (kExtendTileCols * D / 4 / 256));
     hipLaunchKernelGGL((chunk_merge_kernel<D>), grid, dim3(256), 0, s, a);
   }
   const int n_tok = static_cast<int>(p->merge_tok.size());
@@ -2113,11 +2114,12 @@ using namespace pfx;
 extern "C" int pfx_plan_upload(pfx_plan* p, void* ws, size_t bytes, void* stream) {
   if (!p || !ws) return fail(PFX_EINVAL, "pfx_plan_upload: NULL argument");
   if (reinterpret_cast<uintptr_t>(ws) % 256) return fail(PFX_EINVAL, "pfx_plan_upload: workspace not 256-byte aligned");
-  if (bytes < p->total_bytes)
+  if (bytes < p->whole_bytes)
     return fail(PFX_ENOMEM, "pfx_plan_upload: workspace has %zu bytes, plan needs %zu", bytes, p->total_bytes);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (p->blob_bytes) {
-    hipError_t e = hipMemcpyAsync(ws, p->blob.data(), p->blob_bytes, hipMemcpyHostToDevice, s);
+  const size_t tables = bytes < p->total_bytes ? p->off_chunks : p->blob_bytes;
+  if (tables) {
+    hipError_t e = hipMemcpyAsync(ws, p->blob.data(), tables, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "pfx_plan_upload: hipMemcpyAsync");
   }
   p->dev_ws = ws;
@@ -2205,7 +2207,7 @@ static int step_launches(const pfx_pool* pool, const pfx_plan* p, const DevPlan&
                          const void* v_new, const void* q, void* o, float* lse, float sm_scale, hipStream_t s,
                          const char* who) {
   const bool attend = p->num_items > 0 || p->num_segs > 0 || p->num_wide > 0;
-  if (p->num_tokens > 0 && ((p->num_items > 0 && !p->num_chunks) || !attend)) {
+  if (p->num_tokens > 0 && ((p->num_items > 0 && !dp.num_chunks) || !attend)) {
     int rc = launch_append(pool, p, dp, k_new, v_new, s, who);
     if (rc || !attend) return rc;
     return launch_attention(pool, p, dp, q, o, lse, sm_scale, s, who);
@@ -2294,7 +2296,7 @@ extern "C" int pfx_attention_noalloc(const pfx_pool* pool, const pfx_plan* p, co
     hipError_t e = hipMemcpyAsync(ws, p->blob.data(), p->blob_bytes, hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "pfx_attention_noalloc: hipMemcpyAsync");
   }
-  const DevPlan dp = dev_plan(p, ws);
+  const DevPlan dp = dev_plan(p, ws, kScratchBytes);
   if (append) return step_launches(pool, p, dp, k_new, v_new, q, o, lse, sm_scale, s, who);
   return launch_attention(pool, p, dp, q, o, lse, sm_scale, s, who);
 }

@@ -105,7 +105,9 @@ struct ChunkCosts {
 };
 constexpr ChunkCosts kChunkCosts128 = {0.7, 4.5, 0.009, 8.5}, kChunkCosts64 = {0.9, 7.0, 0.006, 10.0};
 
-DevPlan dev_plan(const pfx_plan* p, void* ws) {
+// A workspace without room for cut blocks' states holds the plan with its
+// blocks whole: no pieces table, the decode rows' states in its place.
+DevPlan dev_plan(const pfx_plan* p, void* ws, size_t bytes) {
   unsigned char* base = static_cast<unsigned char*>(ws);
   DevPlan d;
   d.items = reinterpret_cast<const Item*>(base + p->off_items);
@@ -117,8 +119,12 @@ DevPlan dev_plan(const pfx_plan* p, void* ws) {
   d.seg_shape = p->seg_shape;
   d.merge_tok = reinterpret_cast<const int32_t*>(base + p->off_merge_tok);
   d.merge_head = reinterpret_cast<const MergeHead*>(base + p->off_merge_head);
-  d.o_part = reinterpret_cast<uint16_t*>(base + p->off_opart);
-  d.l_part = reinterpret_cast<float*>(base + p->off_lpart);
+  const bool whole = bytes < p->total_bytes;
+  d.num_chunks = whole ? 0 : p->num_chunks;
+  d.num_chunk_merges = whole ? 0 : p->num_chunk_merges;
+  const size_t at = whole ? p->off_chunks : p->off_opart;
+  d.o_part = reinterpret_cast<uint16_t*>(base + at);
+  d.l_part = reinterpret_cast<float*>(base + at + (p->off_lpart - p->off_opart));
   d.chunks = reinterpret_cast<const Chunk*>(base + p->off_chunks);
   d.chunk_merge = reinterpret_cast<const ChunkMerge*>(base + p->off_chunk_merge);
   d.xo_part = reinterpret_cast<float*>(base + p->off_xopart);
@@ -809,10 +815,11 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     p->off_xopart = off;     off = align256(off + size_t(chunk_slots) * kExtendTileCols * p->d * 4);
     p->off_xlpart = off;     off = align256(off + size_t(chunk_slots) * kExtendTileCols * 8);
     p->total_bytes = std::max<size_t>(off, 256);
+    p->whole_bytes = chunk_slots ? std::max<size_t>(p->off_chunks + (p->off_xopart - p->off_opart), 256) : p->total_bytes;
   };
   lay_out();
-  if (chunk_slots && p->total_bytes > PFX_NOALLOC_MAX_WORKSPACE) {
-    // Cut blocks may not be what takes a plan past the static workspace.
+  if (!xparts.empty() && p->total_bytes > PFX_NOALLOC_MAX_WORKSPACE) {
+    // Pieces may not be what takes a plan past the static workspace.
     xparts.clear();
     chunk_slots = 0;
     lay_out();

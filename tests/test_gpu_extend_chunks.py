@@ -113,3 +113,44 @@ def test_fixed_length_rows_do_not_depend_on_the_batch(d):
         n = rows[k[0]]
         assert np.array_equal(RN.to_host_bits(ok[:n]), o[row0[k[0]]:row0[k[0] + 1]])
         assert np.array_equal(lk[:n].cpu().numpy(), l[row0[k[0]]:row0[k[0] + 1]])
+
+
+@pytest.mark.parametrize("case", [CASES[0], CASES[1], CASES[4]], ids=["alone", "mixed", "d64"])
+def test_smaller_workspace_keeps_blocks_whole(case):
+    """A workspace without room for the pieces is taken: the bits are those of
+    whole blocks, through append + attention and through the step, nothing past
+    its end is written, and the allocation-free call still cuts.  One byte less
+    is refused."""
+    hq, hkv, d, plen, reqs = case
+    b = W.make_batch(101, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=512, prefix_len=plen,
+                     agent=[r[0] for r in reqs], suffix_len=[r[1] for r in reqs], n_rows=[r[2] for r in reqs])
+    hv = W.host_values(b, 102)
+    _, o_cut, l_cut = run_and_check(b, hv, f"cut {plen} {reqs}")
+    whole, o_ref, l_ref = run_and_check(b, hv, f"whole {plen} {reqs}", piece_steps=16)
+    least = whole.plan.workspace_bytes()
+    del whole
+    announce(f"workspace of {least} bytes for the same batch")
+    for step in (False, True):
+        ds = RN.DeviceStep(b, hv)
+        assert ds.plan.workspace_bytes() > least
+        ws = torch.full((least + 512,), 0x5A, dtype=torch.uint8, device="cuda")
+        ws = ws[-ws.data_ptr() % 256:]
+        with pytest.raises(B.PfxError) as e:
+            ds.plan.upload(workspace=ws[:least - 1])
+        assert e.value.code == B.PFX_ENOMEM
+        ds.plan.upload(workspace=ws[:least])
+        if step:
+            B.pfx_step(ds.pool, ds.plan, ds.k_new, ds.v_new, ds.q, ds.o, ds.lse)
+        else:
+            ds.step()
+        B.pfx_sync_check()
+        o, l = ds.outputs()
+        assert np.array_equal(o, o_ref) and np.array_equal(l, l_ref)
+        exp_k, exp_v = PT.expected_pools(b, hv)
+        gk, gv = ds.read_pages(hv.pages)
+        assert np.array_equal(gk, exp_k) and np.array_equal(gv, exp_v)
+        assert bool((ws[least:] == 0x5A).all())
+        B.pfx_attention_noalloc(ds.pool, ds.plan, ds.q, ds.o, ds.lse, k_new=ds.k_new, v_new=ds.v_new)
+        B.pfx_sync_check()
+        o, l = ds.outputs()
+        assert np.array_equal(o, o_cut) and np.array_equal(l, l_cut)
