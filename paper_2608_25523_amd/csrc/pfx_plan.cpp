@@ -70,8 +70,14 @@ constexpr int32_t kLongPieceSteps = 64;
 constexpr int64_t kLongPiecesFrom = 32768;
 constexpr int32_t kLeastPieceSteps = 3;
 // Workgroups resident at once on 256 compute units, by the registers: two on
-// each at d = 128, four at d = 64.
-constexpr int64_t kResident128 = 512, kResident64 = 1024;
+// each at d = 128; at d = 64 four of the kernel that runs only pieces on the
+// matrix cores (126 registers), three of the one with wide blocks (147) and of
+// the vector-ALU engine (162).  With wide blocks, d = 64, us a step call with
+// pieces for 1024 workgroups and for 768: 24 requests of one agent over 8192
+// 18.9 and 15.8, 40 over 4096 16.9 and 14.2, 40 of two agents 17.0 and 14.8, 64
+// over 2048 17.1 and 15.5, 32 over 6000 19.7 and 17.6; the vector-ALU engine,
+// 16 over 8192, 31.4 and 30.4.
+constexpr int64_t kResident128 = 512, kResident64 = 1024, kResident64Wide = 768;
 
 // An extend launch of fewer blocks than fit the chip at once (512 workgroups,
 // two on a compute unit) may cut its blocks along their keys.  The launch is
@@ -479,7 +485,9 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     piece_steps = steps >= kLongPiecesFrom                   ? kLongPieceSteps
                   : steps >= kMidPiecesFrom && p->d == 128 ? kMidPieceSteps
                                                            : kDefaultPieceSteps;
-    int64_t room = p->d == 128 ? kResident128 : kResident64;
+    bool wide = false;
+    for (const DItem& x : dit) wide |= x.wide != 0;
+    int64_t room = p->d == 128 ? kResident128 : wide || engine == PFX_DECODE_VALU ? kResident64Wide : kResident64;
     // Beside extend blocks, which take longer, the pieces stay long.
     for (int32_t r = 0; r < R && room > 0; ++r)
       if (p->req[r].n > 0 && !is_decode_class(r)) room = 0;

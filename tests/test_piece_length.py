@@ -74,3 +74,19 @@ def test_short_pieces_have_short_records(reqs, plen, most):
     assert s.num_decode_pieces > long.num_decode_pieces
     tables = s.workspace_bytes - 264 * s.num_partial_rows
     assert tables < most << 10 and tables < 1088 * long.num_decode_pieces
+
+
+@pytest.mark.parametrize("reqs,plen,engine,room", [
+    (24, [8192], B.PFX_DECODE_MFMA, 768), (64, [2048], B.PFX_DECODE_MFMA, 768),
+    (16, [8192], B.PFX_DECODE_MFMA, 1024), (16, [8192], B.PFX_DECODE_VALU, 768)])
+def test_resident_workgroups_of_the_kernel_that_runs(reqs, plen, engine, room):
+    """d = 64: three workgroups of the kernel with wide blocks, or of the
+    vector-ALU engine, fit a compute unit, four of the other."""
+    b = batch(64, reqs, plen)
+    s = plan(b, decode_engine=engine).stats()
+    assert (s.num_wide_blocks > 0) == (reqs > 16)
+    count = {l: plan(b, piece_steps=l, decode_engine=engine).stats() for l in range(3, 17)}
+    fits = [l for l in count if count[l].num_decode_pieces + count[l].num_wide_blocks <= room]
+    want = count[min(fits)]
+    assert (s.num_decode_pieces, s.num_wide_blocks) == (want.num_decode_pieces, want.num_wide_blocks)
+    assert min(fits) > 3
