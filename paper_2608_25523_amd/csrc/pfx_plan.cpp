@@ -138,19 +138,16 @@ DevPlan dev_plan(const pfx_plan* p, void* ws, size_t bytes) {
   return d;
 }
 
-// The piece records of a plan at their full length.
-static std::vector<Seg> full_segs(const pfx_plan* p) {
-  std::vector<Seg> segs(size_t(p->num_segs), Seg{});
+// Piece record k of a plan at its full length.
+static Seg full_seg(const pfx_plan* p, size_t k) {
   const size_t rows = size_t(p->seg_shape.row_vecs) * 16, steps = size_t(p->seg_shape.step_vecs) * 16;
-  const unsigned char* at = p->blob.data() + p->off_segs;
-  for (Seg& sg : segs) {
-    std::memcpy(&sg.h, at, sizeof(SegHead));
-    std::memcpy(sg.tok, at + sizeof(SegHead), rows);
-    std::memcpy(sg.out, at + sizeof(SegHead) + rows, rows);
-    std::memcpy(sg.steps, at + sizeof(SegHead) + 2 * rows, steps);
-    at += size_t(p->seg_shape.vecs()) * 16;
-  }
-  return segs;
+  const unsigned char* at = p->blob.data() + p->off_segs + k * size_t(p->seg_shape.vecs()) * 16;
+  Seg sg{};
+  std::memcpy(&sg.h, at, sizeof(SegHead));
+  std::memcpy(sg.tok, at + sizeof(SegHead), rows);
+  std::memcpy(sg.out, at + sizeof(SegHead) + rows, rows);
+  std::memcpy(sg.steps, at + sizeof(SegHead) + 2 * rows, steps);
+  return sg;
 }
 
 }  // namespace pfx
@@ -1042,17 +1039,12 @@ extern "C" int pfx_plan_export(const pfx_plan* p, int32_t which, int32_t* out, i
   if (!p || !count) return fail(PFX_EINVAL, "pfx_plan_export: NULL argument");
   const int32_t* src = nullptr;
   int64_t n = 0;
-  std::vector<pfx::Seg> segs;  // the records in full
   switch (which) {
     case 0: src = reinterpret_cast<const int32_t*>(p->host_items()); n = int64_t(p->num_items + p->num_wide) * 32; break;
     case 1: src = p->row_tok.data(); n = int64_t(p->row_tok.size()); break;
     case 8: src = p->row_out.data(); n = int64_t(p->row_out.size()); break;
     case 2: src = p->page_list.data(); n = int64_t(p->page_list.size()); break;
-    case 3:
-      n = int64_t(p->num_segs) * 272;
-      if (cap > 0 && out) segs = pfx::full_segs(p);
-      src = reinterpret_cast<const int32_t*>(segs.data());
-      break;
+    case 3: n = int64_t(p->num_segs) * 272; break;  // src stays null: record by record
     case 6: src = p->merge_tok.data(); n = int64_t(p->merge_tok.size()); break;
     case 7: src = reinterpret_cast<const int32_t*>(p->merge_head.data()); n = int64_t(p->merge_head.size()) * 2; break;
     default: return fail(PFX_EINVAL, "pfx_plan_export: which = %d", which);
@@ -1060,7 +1052,11 @@ extern "C" int pfx_plan_export(const pfx_plan* p, int32_t which, int32_t* out, i
   *count = n;
   if (cap > 0 && !out) return fail(PFX_EINVAL, "pfx_plan_export: out is NULL");
   int64_t m = std::min(n, std::max<int64_t>(cap, 0));
-  if (m) std::memcpy(out, src, size_t(m) * 4);
+  if (m && src) std::memcpy(out, src, size_t(m) * 4);
+  for (int64_t at = 0; !src && at < m; at += 272) {
+    const pfx::Seg sg = pfx::full_seg(p, size_t(at / 272));
+    std::memcpy(out + at, &sg, size_t(std::min<int64_t>(272, m - at)) * 4);
+  }
   return PFX_OK;
 }
 

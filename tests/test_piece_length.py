@@ -2,6 +2,8 @@
 with which every workgroup of the launch is resident at once, 16 where none
 is, 32 from 12288 steps on."""
 
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -90,3 +92,15 @@ def test_resident_workgroups_of_the_kernel_that_runs(reqs, plen, engine, room):
     want = count[min(fits)]
     assert (s.num_decode_pieces, s.num_wide_blocks) == (want.num_decode_pieces, want.num_wide_blocks)
     assert min(fits) > 3
+
+
+def test_export_of_part_of_the_records():
+    """pfx_plan_export writes min(cap, size) values of the piece records, also
+    when the cut falls inside one."""
+    p = plan(batch(128, 4, [2048]))
+    full = p.export(3).reshape(-1)
+    for cap in (0, 1, 271, 272, 273, len(full) - 1, len(full) + 5):
+        out, n = np.full(len(full) + 8, -7, np.int32), C.c_int64()
+        assert B.LIB.pfx_plan_export(p.h, 3, out.ctypes.data_as(C.c_void_p), cap, C.byref(n)) == 0
+        m = min(cap, len(full))
+        assert n.value == len(full) and np.array_equal(out[:m], full[:m]) and (out[m:] == -7).all()
