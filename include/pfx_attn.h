@@ -178,10 +178,10 @@ typedef struct pfx_plan_opts {
    * The automatic division follows the batch: a decode row's pieces, and
    * whether the extend blocks of a small launch are cut along their keys, may
    * change with the other requests, and rows then differ by rounding between
-   * batches.  With a fixed length extend blocks stay whole, and the results of
-   * an extend row, and of a decode row without a prefix, follow from their own
-   * request alone.  (Decode rows that share a prefix are computed together, so
-   * those may still differ by rounding with the other rows of their agent.) */
+   * batches.  With a fixed length extend blocks stay whole, and a row's result
+   * follows from its own request and prefix alone, except that the prefix of
+   * an agent with more than 64 decode columns per KV head is summed in another
+   * order (as wide blocks). */
   int32_t piece_steps;
   /* Engine of the decode pieces: PFX_DECODE_MFMA (0, the default: matrix
    * cores, and wide prefix blocks for agents with more than 64 decode

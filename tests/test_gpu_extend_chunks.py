@@ -154,3 +154,51 @@ def test_smaller_workspace_keeps_blocks_whole(case):
         B.pfx_sync_check()
         o, l = ds.outputs()
         assert np.array_equal(o, o_cut) and np.array_equal(l, l_cut)
+
+
+MORE = [
+    # (Hq, Hkv, d, prefixes, requests, rows checked against the oracle)
+    (16, 8, 128, [1500], [(0, 140, 140), (0, 20, 1)], None),     # G = 2
+    (16, 2, 128, [1500], [(0, 70, 70), (0, 33, 33)], None),      # G = 8
+    (6, 3, 64, [2100], [(0, 150, 90), (0, 9, 1)], None),         # 3 KV heads: no head keeps to one XCD
+    (32, 8, 128, [4500], [(0, 1200, 1200)], 40),                 # pieces in two rounds
+    (32, 2, 64, [16], [(0, 1100, 1100)], 60),                    # 276 whole blocks, the second 256 reversed
+    (48, 3, 64, [16], [(0, 700, 700)], 60),                      # 264 whole blocks, not reversed
+]
+
+
+@pytest.mark.parametrize("case", MORE, ids=["g2", "g8", "kv3", "two-rounds", "reversed", "kv3-whole"])
+def test_more_block_shapes(case):
+    """Query groups, KV head counts and launch sizes past those of the cases
+    above: against the oracle (on sampled rows where the batch is large), all
+    rows against whole blocks within twice the rounding of P and O, and the
+    step bit for bit against append + attention."""
+    hq, hkv, d, plen, reqs, sample = case
+    b = W.make_batch(110, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=512, prefix_len=plen,
+                     agent=[r[0] for r in reqs], suffix_len=[r[1] for r in reqs], n_rows=[r[2] for r in reqs])
+    hv = W.host_values_fast(b, 111)
+    rows = None
+    if sample:
+        n = reqs[0][2]
+        rows = {0: sorted({0, 1, 15, 16, 31, 32, n - 1} | set(np.random.default_rng(1).integers(0, n, sample).tolist()))}
+    ds, o, l = run_and_check(b, hv, f"blocks Hq={hq} Hkv={hkv} d={d} {plen} {reqs}", rows=rows)
+    states = ds.plan.workspace_bytes() // (512 * d + 1024)
+    assert states > 512 if plen[0] == 4500 else states < 8 if plen[0] == 16 else 8 < states < 512
+    whole = B.plan_from_batch(ds.pool, b, piece_steps=16).upload()
+    o1, l1 = torch.empty_like(ds.o), torch.empty_like(ds.lse)
+    B.pfx_attention(ds.pool, whole, ds.q, o1, l1)
+    B.pfx_sync_check()
+    # Cut and whole blocks round P (2^-9 of each term) against other maxima, and O: the outputs differ by less than
+    # both roundings of both sides, 4 * 2^-9 of their 2-norm.
+    x, y = ds.o.double(), o1.double()
+    assert float((x - y).norm() / y.norm()) < 2 ** -7 and float((ds.lse - l1).abs().max()) < 1e-2
+    del ds
+    ds = RN.DeviceStep(b, hv)
+    B.pfx_step(ds.pool, ds.plan, ds.k_new, ds.v_new, ds.q, ds.o, ds.lse)
+    B.pfx_sync_check()
+    os, ls = ds.outputs()
+    assert np.array_equal(o, os) and np.array_equal(l, ls)
+    exp_k, exp_v = PT.expected_pools(b, hv)
+    gk, gv = ds.read_pages(hv.pages)
+    assert np.array_equal(gk, exp_k) and np.array_equal(gv, exp_v)
+    assert_untouched(ds, hv.pages, "block shapes")

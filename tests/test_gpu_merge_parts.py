@@ -75,3 +75,24 @@ def test_rows_do_not_depend_on_longer_ones(d, hq, hkv):
         B.pfx_sync_check()
         o1, l1 = ds.outputs()
         assert np.array_equal(o1[0], o2[0]) and np.array_equal(l1[0], l2[0])
+
+
+@pytest.mark.parametrize("d,hq,hkv", [(128, 32, 8), (64, 32, 8)])
+def test_fixed_length_rows_of_an_agent(d, hq, hkv):
+    """At a fixed piece length a request with a prefix has the same bits alone
+    and among 16 of its agent (64 columns: no wide blocks), one of them with
+    more than eight parts."""
+    lens = [50, 1500] + [30 + 13 * i for i in range(14)]
+    b = W.make_batch(430, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=512, prefix_len=[700],
+                     agent=[0] * 16, suffix_len=lens, n_rows=[1] * 16)
+    hv = W.host_values(b, 431)
+    ds, o16, l16 = run_and_check(b, hv, f"16 requests of an agent, d={d}", piece_steps=4)
+    assert ds.plan.stats().num_wide_blocks == 0
+    pp, sp = b.prefix_pages[0], b.suffix_pages
+    for r in (0, 1, 9):
+        one = B.pfx_plan_create(ds.pool, [0, len(pp)], pp, [700], [0], [0, len(sp[r])], sp[r], lens[r:r + 1], [0, 1],
+                                hq, B.PFX_MODE_DECODE, piece_steps=4).upload()
+        o, l = torch.empty_like(ds.o[:1]), torch.empty_like(ds.lse[:1])
+        B.pfx_attention(ds.pool, one, ds.q[r:r + 1], o, l)
+        B.pfx_sync_check()
+        assert np.array_equal(RN.to_host_bits(o)[0], o16[r]) and np.array_equal(l.cpu().numpy()[0], l16[r])
