@@ -743,11 +743,18 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
     int32_t cut = 0, longest = 0;
     if (int64_t(nitems) < kResidentExtend) {
       std::vector<int32_t> length;  // of the blocks in launch order, in pairs; hkv workgroups each
+      struct Run {
+        int32_t length, blocks;
+      };
+      std::vector<Run> runs;  // of equal lengths (short rows against long keys make many)
+      length.reserve(xrank.size());
       int64_t pairs = 0;
       for (int32_t xi : xrank) {
         length.push_back((xsteps(xbs[xi]) + 1) / 2);
         pairs += int64_t(length.back()) * hkv;
         longest = std::max(longest, length.back());
+        if (!runs.empty() && runs.back().length == length.back()) ++runs.back().blocks;
+        else runs.push_back(Run{length.back(), 1});
       }
       // Two workgroups on a compute unit: the longer runs beside the shorter,
       // then alone.
@@ -769,10 +776,10 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
         int64_t c = std::max<int64_t>(kLeastChunkPairs, (pairs + room - 1) / room), count = 0, slots = 0;
         for (; c < longest; c += 1 + c / 32) {  // finer steps would change a piece by less than 3%
           count = slots = 0;
-          for (int32_t n : length) {
-            const int64_t k = (n + c - 1) / c;
-            count += k * hkv;
-            slots += k > 1 ? k * hkv : 0;
+          for (const Run& run : runs) {
+            const int64_t k = (run.length + c - 1) / c;
+            count += k * hkv * run.blocks;
+            slots += k > 1 ? k * hkv * run.blocks : 0;
           }
           if (count <= room) break;
         }
