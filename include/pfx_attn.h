@@ -270,10 +270,12 @@ int pfx_append_kv(const pfx_pool* pool, const pfx_plan* plan, const void* k_new,
  *     O = sum_j softmax_j(sm_scale * q . k_j) v_j,
  * accumulated in fp32 from bf16 inputs.  sm_scale <= 0 selects
  * 1/sqrt(head_dim).  Prefix KV is read once per agent group and KV head;
- * the states of a decode row's pieces are combined with the log-sum-exp
- * merge (as pfx_merge_states), in a second launch on the same stream.
+ * the states of a decode row's pieces (bf16 values, fp32 maximum and sum) and
+ * of a cut extend block's pieces (fp32) are combined with the log-sum-exp
+ * merge (as pfx_merge_states), in launches of their own on the same stream.
  * Results are deterministic: the same plan shape and inputs give
- * bit-identical outputs, wherever the pages sit.  Calls that share a plan
+ * bit-identical outputs, wherever the pages sit (pfx_plan_opts.piece_steps
+ * says how they follow from the rest of the batch).  Calls that share a plan
  * workspace must not overlap.
  * --------------------------------------------------------------------- */
 int pfx_attention(const pfx_pool* pool, const pfx_plan* plan, const void* q, void* o, float* lse,
@@ -283,13 +285,14 @@ int pfx_attention(const pfx_pool* pool, const pfx_plan* plan, const void* q, voi
  * One step: the KV append of the step's new tokens (as pfx_append_kv)
  * followed by attention for every query row (as pfx_attention), with the
  * same results bit for bit, in the fewest launches.  When the plan has no
- * extend blocks, the decode launch appends as it goes: a decode request's
- * new tokens are read straight from k_new / v_new into the step that
- * attends them and written into their pool slots by the same workgroup (no
- * other work of the launch reads those slots).  So do the extend blocks of a
- * small launch; with many or long ones the append runs first as its own
- * launch.  Arguments as pfx_append_kv and pfx_attention; k_new and
- * v_new may be NULL only when the plan has no query rows.
+ * extend blocks, the append is part of the attention launches: a decode
+ * request's new tokens are read straight from k_new / v_new into the step
+ * that attends them, and written into their pool slots beside the merge.  The
+ * extend blocks of a small launch read theirs likewise, and each writes its
+ * own rows (no other work of the launch reads those slots); with many or long
+ * blocks the append runs first as its own launch.  Arguments as
+ * pfx_append_kv and pfx_attention; k_new and v_new may be NULL only when the
+ * plan has no query rows.
  * --------------------------------------------------------------------- */
 int pfx_step(const pfx_pool* pool, const pfx_plan* plan, const void* k_new, const void* v_new, const void* q,
              void* o, float* lse, float sm_scale, void* hip_stream);
@@ -316,8 +319,9 @@ int pfx_merge_states(const float* o_parts, const float* lse_parts, int32_t num_p
  * host memory (hipHostMalloc), so the same call loads (host -> GPU) and
  * evicts (GPU -> host).  src_pages and dst_pages are host arrays, checked
  * against the two page counts (PFX_ERANGE) and for repeated destinations
- * (PFX_EINVAL) before anything runs; they are staged in the caller's device
- * workspace (at least pfx_page_copy_workspace_bytes(n) bytes).  A page
+ * (PFX_EINVAL) before anything runs.  Lists of up to 448 pages travel with the
+ * launch, longer ones are staged in the caller's device workspace (at least
+ * pfx_page_copy_workspace_bytes(n) bytes, required for any n).  A page
  * array that is neither device memory nor pinned host memory is rejected
  * (PFX_EINVAL) before anything runs.
  * --------------------------------------------------------------------- */
@@ -333,10 +337,10 @@ int pfx_page_copy(const pfx_pool* dst, const pfx_pool* src, const int32_t* dst_p
  * are given) followed by pfx_attention on the same plan, bit for bit; the
  * plan need not be uploaded and no caller workspace is used.  Instead the
  * plan's tables (copied from its host image on the stream at every call)
- * and the decode pieces' partial states live in a static device array of
- * PFX_NOALLOC_MAX_WORKSPACE bytes, which each GPU the library runs on holds
- * until the process ends.  The call allocates nothing: no hipMalloc, no
- * hipFree.
+ * and the partial states of decode pieces and of cut extend blocks live in a
+ * static device array of PFX_NOALLOC_MAX_WORKSPACE bytes, which each GPU the
+ * library runs on holds until the process ends.  The call allocates nothing:
+ * no hipMalloc, no hipFree.
  *   k_new, v_new  as pfx_append_kv, or both NULL to skip the append;
  *   q, o, lse, sm_scale  as pfx_attention.
  * Errors: PFX_ENOMEM, before anything runs, when the plan's workspace

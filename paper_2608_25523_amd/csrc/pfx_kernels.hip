@@ -1294,7 +1294,7 @@ __global__ __launch_bounds__(256, 2) void extend_kernel(AttnArgs a) {
 
 // Pieces of extend blocks.  A launch of few blocks is bound by the steps of one
 // block in series (300 rows over 4096 keys, Hq 32, Hkv 8, d 128: 80 blocks of
-// 69 pairs on 256 compute units, 92 us a step call with the append; as 480
+// 69 pairs on 256 compute units, 93 us a step call with the append; as 480
 // pieces 39 us, of which the pieces take about 24 and their merge 8).
 template <int D, bool A>
 __global__ __launch_bounds__(256, 2) void extend_chunk_kernel(AttnArgs a) {
@@ -1981,11 +1981,11 @@ __global__ __launch_bounds__(256) void page_copy_kernel(const u32x4* src_k, cons
 
 // Reads from host memory are bound by the link (57 GB/s by the copy engines),
 // which 64 workgroups of one load a thread keep busy.  More requests at once
-// only queue on the way: 128 pages (8.4 MB) took 192 us with a workgroup for
-// every 4 KiB, here about 152, and the decode attention beside a 134 MB load 71
-// us a call, here 57 (29 alone).  Writes to host memory gain nothing from it
-// (154 us either way) and are gentler on attention with all workgroups at once
-// (54 us a call against 96).
+// only queue on the way: 128 pages (8.4 MB) took 197 us with a workgroup for
+// every 4 KiB, here 150, and the decode attention beside a 134 MB load 68 us a
+// call, here 49 (30 alone).  Writes to host memory gain nothing from it (154
+// us either way) and are gentler on attention with all workgroups at once (53
+// us a call against 96).
 constexpr int kLinkWorkgroups = 64;
 
 template <typename Pairs>
@@ -2031,11 +2031,14 @@ static int check_pool_matches(const pfx_pool* pool, const pfx_plan* p, const cha
 // half of the compute units and the next on the others), for as long as both
 // last: a unit then holds one of each instead of the two kinds following one
 // another.  448 requests of 8 agents, 8192-token prefixes, Hq 64 (1024 blocks,
-// 3584 pieces) 482 -> 440 us; 320 of 6 (640, 2560) 260 -> 239; 400 of 4 at Hq
-// 32 (256, 3200) 127.3 -> 121.4; fewer blocks than a run stay in front, and so
-// do blocks with more steps than the pieces (56 requests of 25 to 50 tokens of
-// their own over 8192: the blocks wait behind short pieces, 32.6 -> 34.9).  Runs
-// of 8 put two blocks on every other unit (400 requests: 144 us), runs of 512
+// 3584 pieces) 482 -> 441 us; 320 of 6 with 500 to 2048 tokens of their own
+// (768, 2560) 397 -> 369; 400 of 4 over 4096 at Hq 32 (256, 3200) 129 -> 123;
+// fewer blocks than a run stay in front, and so do blocks with more steps than
+// the pieces, which would wait behind short ones (56 requests of 25 to 50
+// tokens of their own over 8192: 22.6 us, dealt 26.9; nearer the line it would
+// still gain: 200 of two agents, 16384 block steps, 94 us, dealt 89 beside
+// 15736 piece steps, and 57.0, dealt 56.3, beside 2640).  Runs of 8 put two
+// blocks on every other unit (400 requests: 144 us), runs of 512
 // change nothing; at d = 64, four workgroups a unit, runs of 128 lose 2%.  In
 // front of a mixed batch the extend blocks stay together (spread among the
 // pieces they ran 5% slower).

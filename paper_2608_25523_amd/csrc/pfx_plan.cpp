@@ -43,19 +43,22 @@ static int64_t pages_for(int64_t tokens) { return (tokens + PFX_PAGE_SIZE - 1) /
 // turn over 16 pools (nothing of K/V left in the last-level cache), Hq 32,
 // Hkv 8, d 128, us per step call.
 //   From kLongPiecesFrom steps on: 64.
-//   From kMidPiecesFrom on at d = 128: 32.  100 requests of 4 agents (13464 steps) 51.9
-//   at 16, 49.4 at 32, 65.0 at 64; 160 of 8 (25408) 90.2, 85.8, 86.2; 64
-//   requests of 4 agents (7032) 30.0 at 16, 38.9 at 32.  At d = 64 it gains
-//   nothing (24286 steps: 49.5 at 16, 49.8 at 32).
-//   Below: the shortest from kLeastPieceSteps on with which the whole launch
-//   is resident at once, else 16.  A launch that size is bound by its longest
-//   workgroup, about 0.75 us a step after 4.5 us of start, not by memory, and
-//   one workgroup past the resident ones waits for a whole piece to end.  At
-//   16-step pieces and at this rule's (pieces): one request over 2048 + 288
-//   keys 18.6 -> 10.4 (3 steps, 200); 4 requests of one agent 19.2 -> 11.3 (3,
-//   280); 16 of three agents 20.4 -> 16.9 (7, 456); 32 of four 21.7 -> 20.1
-//   (11, 496).  Two steps a piece: 11.8 and 12.8 for the first two.  More
-//   workgroups than fit: 19.5 (6, 528) and 21.3 (6, 744) for the last two.
+//   From kMidPiecesFrom on at d = 128: 32.  Batches of four agents at 16 and
+//   32 steps a piece: 9520 steps 38.4 and 42.2, 10944 41.5 and 42.2, 11960
+//   46.7 and 45.5, 12352 48.9 and 46.0, 15344 56.2 and 55.0; at 64, 13464
+//   steps take 65.0 for 49.4 at 32.  At d = 64 it gains nothing (24286 steps:
+//   49.5 at 16, 49.8 at 32).
+//   Below: 16.
+//   Where a shorter length, of kLeastPieceSteps or more, keeps the whole launch
+//   resident at once: the shortest such.  A launch that size is bound by its
+//   longest workgroup, about 0.75 us a step after 4.5 us of start, not by
+//   memory, and one workgroup past the resident ones waits for a whole piece to
+//   end.  At 16-step pieces and at this rule's (pieces): one request over 2048 +
+//   288 keys 18.6 -> 10.9 (3 steps, 200); 4 requests of one agent 19.0 -> 12.3
+//   (3, 320); 16 of three agents 20.5 -> 16.9 (7, 456); 32 of four 23.1 -> 22.2
+//   (12, 448); one over 49280 keys (12328 steps) 51.1 -> 44.8 (25, 504), 46.4
+//   at 32.  Two steps a piece: 11.8 for the first.  More workgroups than fit:
+//   19.5 (6, 528) for the third.
 //   A request without a prefix whose keys fit one piece of 16 steps keeps
 //   them in one: its sums stay fp32 until the one rounding of its state, which
 //   the merge of a lone part repeats exactly.  In 3-step pieces a row of 288
@@ -92,19 +95,23 @@ constexpr int64_t kResident128 = 512, kResident64 = 1024, kResident64Wide = 768;
 // The blocks are cut when that saves a tenth, and never at a fixed piece
 // length: how a row is summed then does not follow from the rest of the batch,
 // and the workspace holds no states of theirs.  Measured, us a step call uncut
-// and cut, Hq 32, Hkv 8, d 128: 300 rows over 4096 keys (80 blocks of 69
-// pairs) 92 and 39; 32 rows over 4096 (8 of 65) 86 and 21; 700 over 8192 (176
-// of 139) 178 and 128; 1000 over 4096 (256 of 80) 107 and 90; left uncut: 1999
-// over 2048 (504 of 64) 110 and 115, 8 requests of 30 to 100 over 1000 (176 of
-// 18) 31.5 and 32.7.
+// and cut (each step over another of 12 pools), Hq 32, Hkv 8, d 128: 300 rows
+// over 4096 keys (80 blocks of 69 pairs) 93 and 39; 32 rows over 4096 (8 of 65)
+// 87 and 19; 700 over 8192 (176 of 139) 180 and 117; 1000 over 4096 (256 of 80)
+// 108 and 88; left uncut: 1999 over 2048 (504 of 64), cut 5% slower, 8 requests
+// of 30 to 100 over 1000 (176 of 18), cut 4% slower.
+// At d = 64 the registers would let a third workgroup onto a unit; the rule
+// and its costs are those of two.
 constexpr int64_t kResidentExtend = 512, kComputeUnits = 256;
 constexpr int32_t kLeastChunkPairs = 4;
 // The launch over a pieces table can also take the step's append along
 // (pfx_step), which costs its loop some registers and the tiles of new tokens
 // a longer issue.  Blocks that stay whole go through the table only when none
-// is longer than this: 4 requests of 32 rows over 128 keys 10.6 -> 9.1 us a
-// step call, but 512 rows over 2048 at Hq 64 (40 pairs) 59.0 -> 61.3.  Cut
-// launches gain: 32 rows over 4096 keys 20.7 -> 19.1, 300 39.8 -> 38.4.
+// is longer than this.  4 requests of 32 rows, us a step call: over 128 keys
+// 12.4 -> 11.6 (d = 128) and 11.3 -> 9.0 (Hq 8, Hkv 2, d = 64); over 500 (9
+// pairs) 19.2 -> 19.8 and, Hq 32, d = 64, 16.4 -> 15.7; over 700 (12) 22.6 ->
+// 23.4 and 19.1 -> 18.4; 512 rows over 2048 at Hq 64 (40) 59.0 -> 61.3: the
+// line is that of d = 128.  Cut launches gain about 1.5 us by it.
 constexpr int32_t kShortPairs = 8;
 struct ChunkCosts {
   double alone, fixed, slot, late;
@@ -716,8 +723,8 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
   // When no compute unit runs more than two blocks, workgroup i shares one with
   // workgroup 256 + i: the second 256 go shortest first, so that the longest
   // block has the shortest beside it.  504 blocks, 1999 rows over 2048 keys:
-  // 110.8 -> 107.6 us a step call at d = 128, 74.5 -> 73.2 at d = 64; 2000 rows
-  // over 16 keys 56.4 -> 54.0; where the lengths hardly differ nothing changes.
+  // 107.1 -> 103.4 us a step call at d = 128, 74.9 -> 73.8 at d = 64; 2000 rows
+  // over 16 keys 57.2 -> 54.7; where the lengths hardly differ nothing changes.
   // (Beside decode pieces the launch is fuller than that.)
   if (int64_t(nitems) > kComputeUnits && int64_t(nitems) <= kResidentExtend && npcs == 0 && kComputeUnits % hkv == 0)
     std::reverse(xrank.begin() + kComputeUnits / hkv, xrank.end());
@@ -769,8 +776,8 @@ extern "C" int pfx_plan_create(const pfx_pool* pool, const pfx_prefix_table* pt,
       // The shortest pieces that leave every workgroup half a compute unit,
       // with the decode pieces after them or beside them, or a whole one; or
       // pieces in two rounds, where all blocks cut in two are too many for one
-      // (304 blocks: 1200 rows over 8192 keys 236 -> 191 us a step call, two
-      // requests of 600 over 6000 177 -> 148).
+      // (304 blocks: 1200 rows over 8192 keys 235 -> 188 us a step call, two
+      // requests of 600 over 6000 174 -> 145).
       for (int64_t room : {kResidentExtend, kResidentExtend - int64_t(npcs), kComputeUnits, 2 * kResidentExtend}) {
         if (room < kComputeUnits || fixed_division) continue;
         int64_t c = std::max<int64_t>(kLeastChunkPairs, (pairs + room - 1) / room), count = 0, slots = 0;

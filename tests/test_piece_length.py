@@ -1,6 +1,6 @@
-"""The default decode piece length (host only): the shortest from 3 steps on
-with which every workgroup of the launch is resident at once, 16 where none
-is, 32 from 12288 steps on."""
+"""The default decode piece length (host only): 16 steps, 32 from 12288 steps
+on, or the shortest from 3 on with which every workgroup of the launch is
+resident at once, where that is shorter; and the piece records."""
 
 import ctypes as C
 
@@ -42,6 +42,17 @@ def test_shortest_length_that_is_resident(d, reqs, plen, extend):
     fits = [l for l in count if count[l].num_decode_pieces + count[l].num_wide_blocks <= room]
     want = count[min(fits) if fits else 16]
     assert (s.num_decode_pieces, s.num_wide_blocks) == (want.num_decode_pieces, want.num_wide_blocks)
+
+
+def test_length_of_few_long_items():
+    """One long request past 12288 steps: as many pieces as are resident, more
+    than 32-step pieces would be."""
+    b = W.make_batch(7, num_q_heads=32, num_kv_heads=8, head_dim=128, num_pages=4096, prefix_len=[49000], agent=[0],
+                     suffix_len=[280], n_rows=[1])
+    s = plan(b).stats()
+    assert 12288 <= s.num_decode_steps < 16384
+    assert plan(b, piece_steps=32).stats().num_decode_pieces < s.num_decode_pieces <= 512
+    assert plan(b, piece_steps=24).stats().num_decode_pieces > 512
 
 
 def test_length_of_larger_launches():
