@@ -1780,7 +1780,13 @@ struct MergeSource {
 template <int D>
 __device__ __forceinline__ MergeSource merge_source(const AttnArgs& a, const MergeSpot& s) {
   const size_t unit = size_t(s.m) * a.hkv + (s.qh >> a.group_shift);
-  const MergeHead mh = a.merge_parts ? MergeHead{int32_t(unit) * a.merge_parts, a.merge_parts} : a.plan.merge_head[unit];
+  MergeHead mh = {int32_t(unit) * a.merge_parts, a.merge_parts};
+  if (!a.merge_parts) {
+    mh = a.plan.merge_head[unit];
+    // Waited for here: after the branch, the wait would also hold up the parts
+    // of rows that need no load for the append's chunks in flight.
+    asm volatile("" : "+v"(mh.base), "+v"(mh.nparts));
+  }
   const int g = s.qh & (a.group - 1);
   const size_t row0 = size_t(mh.base) * a.group + g;
   MergeSource r;
