@@ -202,3 +202,35 @@ def test_more_block_shapes(case):
     gk, gv = ds.read_pages(hv.pages)
     assert np.array_equal(gk, exp_k) and np.array_equal(gv, exp_v)
     assert_untouched(ds, hv.pages, "block shapes")
+
+
+@pytest.mark.parametrize("case", [CASES[1], STEPS[0]], ids=["cut", "mixed"])
+def test_captured_step(case):
+    """pfx_step over cut blocks and decode rows captured into a graph and
+    replayed, other work and a fresh pool between the replays: each replay
+    equals the eager step bit for bit."""
+    hq, hkv, d, plen, reqs = case
+    b = W.make_batch(120, num_q_heads=hq, num_kv_heads=hkv, head_dim=d, num_pages=512, prefix_len=plen,
+                     agent=[r[0] for r in reqs], suffix_len=[r[1] for r in reqs], n_rows=[r[2] for r in reqs])
+    hv = W.host_values(b, 121)
+    ds = RN.DeviceStep(b, hv)
+    first = ds.k_pool.clone(), ds.v_pool.clone()
+    announce(f"captured step over {plen} {reqs}")
+    B.pfx_step(ds.pool, ds.plan, ds.k_new, ds.v_new, ds.q, ds.o, ds.lse)
+    B.pfx_sync_check()
+    want = [t.clone() for t in (ds.o, ds.lse, ds.k_pool, ds.v_pool)]
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        B.pfx_step(ds.pool, ds.plan, ds.k_new, ds.v_new, ds.q, ds.o, ds.lse,
+                   stream=torch.cuda.current_stream().cuda_stream)
+    for _ in range(3):
+        for t, f in ((ds.k_pool, first[0]), (ds.v_pool, first[1])):
+            t.copy_(f)
+        ds.o.zero_()
+        ds.lse.zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for t, w in zip((ds.o, ds.lse, ds.k_pool, ds.v_pool), want):
+            assert torch.equal(t.view(torch.int16) if t.dtype == torch.bfloat16 else t,
+                               w.view(torch.int16) if w.dtype == torch.bfloat16 else w)
